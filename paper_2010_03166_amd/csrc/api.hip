@@ -218,6 +218,13 @@ GemmBatch with_mode(GemmBatch b, int32_t mode) {
   b.mode = mode;
   return b;
 }
+// The forward product's or input gradient's batch: with split products its
+// weights come as planes.
+GemmBatch with_planes(GemmBatch b, int32_t mode) {
+  b.mode = mode;
+  b.b_planes = mode == GEMM_SPLIT;
+  return b;
+}
 
 LayerLayout layer_layout(const gnn_csr* csr, const gnn_layer* L) {
   LayerLayout o;
@@ -242,8 +249,8 @@ LayerLayout layer_layout(const gnn_csr* csr, const gnn_layer* L) {
   const int32_t bf = gemm_mode(L->flags);
   const size_t gemm_w = gemm_workspace_bytes(with_mode(dw_batch(o.order, n, f_in, h, 0, f_in, 0, 0, 0, 2 * h, 0, 2 * h, 0, 0), bf));
   const size_t gemm = std::max(
-      gemm_workspace_bytes(with_mode(fwd_batch(o.order, n, f_in, h, 0, f_in, 0, 0, 0, 0, 0, 0, 0, 2 * h, 0, 0), bf)),
-      gemm_workspace_bytes(with_mode(dx_batch(o.order, n, f_in, h, 0, 2 * h, 0, 2 * h, 0, 0, 0, f_in, 0, f_in), bf)));
+      gemm_workspace_bytes(with_planes(fwd_batch(o.order, n, f_in, h, 0, f_in, 0, 0, 0, 0, 0, 0, 0, 2 * h, 0, 0), bf)),
+      gemm_workspace_bytes(with_planes(dx_batch(o.order, n, f_in, h, 0, 2 * h, 0, 2 * h, 0, 0, 0, f_in, 0, f_in), bf)));
   // split products: W_self and W_neigh as bf16 pieces in the forward
   // product's orientation (K = f_in, N = h) in the workspace; the input
   // gradient's (K = h, N = f_in) in the saved buffer
@@ -432,13 +439,6 @@ gnn_status gnn_spmm_gather_floor(const gnn_csr* csr, int32_t transpose,
   return GNN_OK;
 }
 
-// Split products pre-split B into its bf16 pieces once (workspace, after
-// the partial tiles) when at least four row tiles of 128 share it: each
-// would otherwise split the same values again.
-static bool gemm_presplit_b(int32_t M, int32_t mode) {
-  return mode == GEMM_SPLIT && M >= 512;
-}
-
 size_t gnn_gemm_workspace_bytes(int32_t M, int32_t N, int32_t K) {
   if (M < 0 || N < 0 || K < 0) return 0;
   GemmBatch b;
@@ -452,10 +452,11 @@ size_t gnn_gemm_workspace_bytes(int32_t M, int32_t N, int32_t K) {
   size_t need = 0;
   for (const int32_t mode : {GEMM_SPLIT, GEMM_BF16, GEMM_F32}) {
     b.mode = mode;
+    b.b_planes = gemm_use_planes(M, mode);
     need = std::max(need, gemm_workspace_bytes(b));
   }
   const size_t part = round_up(need, 256);
-  return part + (gemm_presplit_b(M, GEMM_SPLIT) ? round_up(b_planes_words(K, N) * 4, 256) : 0);
+  return part + (gemm_use_planes(M, GEMM_SPLIT) ? round_up(b_planes_words(K, N) * 4, 256) : 0);
 }
 
 gnn_status gnn_gemm(int32_t trans_a, int32_t trans_b, int32_t M, int32_t N,
@@ -485,8 +486,10 @@ gnn_status gnn_gemm(int32_t trans_a, int32_t trans_b, int32_t M, int32_t N,
   b.p[0].N = N;
   b.p[0].C = C;
   b.p[0].ldc = ldc;
+  // B split into its pieces once (workspace, after the partial tiles)
+  const bool presplit = K > 0 && gemm_use_planes(M, b.mode);
+  b.b_planes = presplit;
   const size_t part = round_up(gemm_workspace_bytes(b), 256);
-  const bool presplit = K > 0 && gemm_presplit_b(M, b.mode);
   const size_t need = part + (presplit ? round_up(b_planes_words(K, N) * 4, 256) : 0);
   if (workspace_bytes < need || (need > 0 && !workspace))
     return GNN_ERR_WORKSPACE;
@@ -499,7 +502,6 @@ gnn_status gnn_gemm(int32_t trans_a, int32_t trans_b, int32_t M, int32_t N,
     uint32_t* planes = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + part);
     const SplitJob job = {B, ldb, K, N, trans_b != 0, planes};
     GNN_HIP(split_b_planes_launch(&job, 1, stream));
-    b.b_planes = 1;
     b.p[0].seg[0].Bp = planes;
     b.p[0].seg[0].bp_plane = (int64_t)(b_planes_words(K, N) / 3);
   }

@@ -10,6 +10,8 @@
 //     Henry, Tang and Heinecke, 2019).  Six 16-deep bf16 MFMAs take 192
 //     cycles against 512 for the eight 2-deep fp32 MFMAs that cover the same
 //     16 k, and the result is as accurate (measured against fp64);
+//     (gemm_planes_kernel: the same products with B's pieces given and
+//     16 x 16 x 32 MFMAs, for forward products and input gradients);
 //   fp32 (gemm_f32_kernel): v_mfma_f32_32x32x2_f32, described below;
 //   bf16 (gemm_bf16_kernel): operands rounded to bf16, one product.
 //
@@ -49,6 +51,8 @@
 // Blocks are numbered so that each XCD (blocks are dispatched round-robin
 // over the 8 XCDs) works on a contiguous range of iterations: the tiles of a
 // row band (same A rows) or the same K range stay in one XCD's L2.
+#include <type_traits>
+
 #include "internal.hpp"
 
 namespace gnnprop {
@@ -77,6 +81,7 @@ struct GemmKArgs {
   int64_t iters;       // tiles * ktiles
   int32_t nblocks;     // P
   int32_t splits;      // > 1: split-K mode, one (tile, K range) per block
+  int32_t bn;          // tile width
   float* part;         // partial tiles (2 per block stream-K, 1 split-K)
   int32_t vec_a, vec_b;
   int32_t vec_c[2];    // C (and mask, bias) of problem i take float4 accesses
@@ -108,23 +113,6 @@ __device__ inline float4 load4(const float* base, int64_t ld, int r, int c,
   return v;
 }
 
-// Element (r, c..c+1) of a row-major R x C matrix, zeros outside; `vec`
-// (8-byte aligned rows, c even) allows one 8-byte load.
-__device__ inline float2 load2(const float* base, int64_t ld, int r, int c, int R, int C,
-                               bool vec) {
-  float2 v = make_float2(0.f, 0.f);
-  if (r < R && c < C) {
-    const float* p = base + (int64_t)r * ld + c;
-    if (vec && c + 1 < C) {
-      v = *reinterpret_cast<const float2*>(p);
-    } else {
-      v.x = p[0];
-      if (c + 1 < C) v.y = p[1];
-    }
-  }
-  return v;
-}
-
 __device__ inline int64_t block_lo(int b, int64_t iters, int nblocks) {
   return (int64_t)b * iters / nblocks;
 }
@@ -150,15 +138,15 @@ struct TileInfo {
   int pi, m0, n0, r0, c0;
 };
 
-__device__ inline TileInfo tile_info(const GemmKArgs& g, int t) {
+__device__ inline TileInfo tile_info(const GemmKArgs& g, int t, int bn) {
   TileInfo ti;
   const int tm = t / g.tiles_n, j = t % g.tiles_n;
   ti.pi = (g.nprob > 1 && j >= g.tiles_n0) ? 1 : 0;
   ti.r0 = tm * BM;
-  ti.c0 = (ti.pi ? j - g.tiles_n0 : j) * BN;
+  ti.c0 = (ti.pi ? j - g.tiles_n0 : j) * bn;
   const int N = ti.pi ? g.p[1].N : g.p[0].N;
   ti.m0 = (g.M >= BM && ti.r0 + BM > g.M) ? g.M - BM : ti.r0;
-  ti.n0 = (N >= BN && ti.c0 + BN > N) ? N - BN : ti.c0;
+  ti.n0 = (N >= bn && ti.c0 + bn > N) ? N - bn : ti.c0;
   return ti;
 }
 
@@ -278,7 +266,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // consecutive columns per thread of a 256-thread block.  Run by
 // gemm_fixup_kernel, or by extra blocks at the end of the next GEMM launch
 // on the stream (which reads the partials the earlier launch wrote).
-constexpr int FIX_CHUNKS = BM * BN / 1024;
+__host__ __device__ inline int fix_chunks(int bn) { return BM * bn / 1024; }
 
 __device__ inline void fixup_chunk(const GemmKArgs& g, int t, int chunk) {
   const int64_t first = (int64_t)t * g.ktiles, last = first + g.ktiles - 1;
@@ -288,16 +276,17 @@ __device__ inline void fixup_chunk(const GemmKArgs& g, int t, int chunk) {
     b1 = block_of(last, g.iters, g.nblocks);
     if (b0 == b1) return;  // written directly by its only block
   }
-  const TileInfo ti = tile_info(g, t);
+  const TileInfo ti = tile_info(g, t, g.bn);
   const GemmProblem& P = ti.pi ? g.p[1] : g.p[0];
   const int e = chunk * 1024 + threadIdx.x * 4;
-  const int rl = e / BN, cl = e % BN;
+  const int rl = e / g.bn, cl = e % g.bn;
+  const int64_t tile = (int64_t)BM * g.bn;
   const int row = ti.m0 + rl, col = ti.n0 + cl;
   if (row >= g.M || col >= P.N || row < ti.r0) return;
   float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
   if (g.splits > 1) {
-    const float* src = g.part + (int64_t)t * (BM * BN) + e;
-    const int64_t st = (int64_t)g.tiles * (BM * BN);
+    const float* src = g.part + t * tile + e;
+    const int64_t st = g.tiles * tile;
     int sp = 0;
     for (; sp + 4 <= g.splits; sp += 4) {  // four partials in flight, in order
       float4 p[4];
@@ -322,7 +311,7 @@ __device__ inline void fixup_chunk(const GemmKArgs& g, int t, int chunk) {
     for (int b = b0; b <= b1; ++b) {
       // the tile is block b's first tile iff b's range starts inside it
       const int slot = block_lo(b, g.iters, g.nblocks) >= first ? 0 : 1;
-      const float4 p = ld4(g.part + ((int64_t)b * 2 + slot) * (BM * BN) + e);
+      const float4 p = ld4(g.part + ((int64_t)b * 2 + slot) * tile + e);
       v.x += p.x;
       v.y += p.y;
       v.z += p.z;
@@ -348,12 +337,13 @@ __global__ __launch_bounds__(256) void gemm_fixup_kernel(GemmKArgs g) {
 }
 
 // Blocks past the GEMM's own run the chunks of a reduction left by the
-// previous launch (`fx`, fx.tiles x FIX_CHUNKS of them); true for those.
+// previous launch (`fx`, fx.tiles x fix_chunks of them); true for those.
 __device__ inline bool run_pending_fixup(const GemmKArgs& g, const GemmKArgs& fx) {
   if ((int)blockIdx.x < g.nblocks) return false;
   if (threadIdx.x >= 256) return true;  // a chunk takes 256 threads
   const int f = (int)blockIdx.x - g.nblocks;
-  fixup_chunk(fx, f / FIX_CHUNKS, f % FIX_CHUNKS);
+  const int chunks = fix_chunks(fx.bn);
+  fixup_chunk(fx, f / chunks, f % chunks);
   return true;
 }
 
@@ -397,7 +387,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmKArgs g, GemmKArgs
     const int kbeg = (int)(it - (int64_t)t * g.ktiles);
     const int kend = (int)min<int64_t>(g.ktiles, hi - (int64_t)t * g.ktiles);
     it = (int64_t)t * g.ktiles + kend;
-    const TileInfo ti = tile_info(g, t);
+    const TileInfo ti = tile_info(g, t, BN);
     const GemmProblem& P = ti.pi ? g.p[1] : g.p[0];
     const int N = P.N;
     const int m0 = ti.m0, n0 = ti.n0;
@@ -768,7 +758,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(GemmKArgs g, GemmKArg
     const int kbeg = (int)(it - (int64_t)t * g.ktiles);
     const int kend = (int)min<int64_t>(g.ktiles, hi - (int64_t)t * g.ktiles);
     it = (int64_t)t * g.ktiles + kend;
-    const TileInfo ti = tile_info(g, t);
+    const TileInfo ti = tile_info(g, t, BN);
     const GemmProblem& P = ti.pi ? g.p[1] : g.p[0];
     const int N = P.N;
     const int m0 = ti.m0, n0 = ti.n0;
@@ -955,6 +945,18 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(GemmKArgs g, GemmKArg
   }
 }
 
+// Transposing LDS read: among 16 lanes, lane l gets column l of the four
+// 32-byte rows of 16 bf16 that lanes 0-3, 4-7, 8-11 and 12-15 address.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ inline s16x4 lds_read_tr(const uint32_t* p) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (__attribute__((address_space(3))) s16x4*)(uint32_t*)p);
+#else
+  return s16x4{};
+#endif
+}
+
 // ----------------------------------------------- split-product kernel
 //
 // The default fp32 mode.  Each operand value is split once per block, as it
@@ -968,18 +970,19 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(GemmKArgs g, GemmKArg
 //   K-contiguous operand: plane [x][k] rows of 8 words (k pairs) + 4 words
 //     of padding (48 bytes: eight consecutive rows of a 128-bit fragment
 //     read fall on distinct banks); a fragment is one 128-bit read.
-//   X-contiguous operand: plane rows of k pairs, word (kp, x) = (k 2kp,
-//     2kp + 1) of column x; pairs 4..7 start 32 words past the end of pairs
-//     0..3 so that the two lane halves of a read use different banks; a
-//     fragment is 4 words from 4 pair rows.
+//   X-contiguous operand: planes of 16-column panels, [x / 16][k][x % 16]
+//     bf16 (rows of 32 bytes; panels 8 words apart in bank, so that the
+//     panels of a row's stores use different banks); a fragment is two
+//     transposing 64-bit reads (k-pair words took four 32-bit reads).
 constexpr int BKS = 16;
 constexpr int KCS_ROW = 12;
 constexpr int KCS_PLANE = 128 * KCS_ROW;
-constexpr int XCS_HALF = 4 * 128 + 32;
-constexpr int XCS_PLANE = 2 * XCS_HALF;
+constexpr int XCS_PANEL = BKS * 8 + 8;  // words
+constexpr int XCS_PLANE = 8 * XCS_PANEL;
 
-__device__ inline int xcs_word(int kp, int x) {
-  return (kp >> 2) * XCS_HALF + (kp & 3) * 128 + x;
+// Word of element (k, x) (x even) of an x-contiguous plane.
+__device__ inline int xcs_word(int k, int x) {
+  return (x >> 4) * XCS_PANEL + k * 8 + ((x & 15) >> 1);
 }
 
 // Pieces of the pair (x0, x1): hi, mid and lo packed as bf16x2 words with
@@ -1001,41 +1004,35 @@ __device__ inline void split3(float x0, float x1, uint32_t& h, uint32_t& m,
   l = pack_bf16(s0, s1);
 }
 
-// BD: B comes pre-split (GemmSeg::Bp, split_b_planes_launch) and each
-// wavefront loads its B fragments straight from those planes into registers
-// (one 128-bit load per piece and block: the planes are in fragment order,
-// so a fragment is 1 KiB of consecutive bytes), one stage ahead of the
-// products that use them; only A goes through the split and LDS.
 // NW: wavefronts per block.  4: each computes 64 x 64 of the 128 x 128
-// tile.  8 (k-contiguous A): each computes 64 x 32, four wavefronts per
-// SIMD at two blocks per CU; a thread stages one float4 of a k-contiguous
-// operand, or two columns of one k pair of an x-contiguous one, per stage.
-template <bool AT, bool BT, bool BD, int NW = 4>
+// tile.  8: each computes 64 x 32, four wavefronts per
+// SIMD at two blocks per CU; a thread stages one float4 of an operand per
+// stage.
+template <bool AT, bool BT, int NW = 4>
 __global__ __launch_bounds__(NW * 64, NW / 2) void gemm_split_kernel(GemmKArgs g, GemmKArgs fx) {
-  static_assert(NW == 4 || (NW == 8 && !AT), "8 wavefronts: k-contiguous A");
+  static_assert(NW == 4 || NW == 8, "wavefronts per block");
   constexpr int NJ = NW == 8 ? 1 : 2;  // 32-column blocks per wavefront
-  constexpr int AP = 8 / NW;           // 64-row groups of A staged per thread
+  constexpr int AP = 8 / NW;           // float4s of an operand staged per thread
   if (run_pending_fixup(g, fx)) return;
   constexpr bool A_KC = !AT;
   constexpr bool B_KC = BT;
   constexpr int A_PLANE = A_KC ? KCS_PLANE : XCS_PLANE;
   constexpr int B_PLANE = B_KC ? KCS_PLANE : XCS_PLANE;
-  constexpr int B_WORDS = BD ? 4 : 3 * B_PLANE;
+  constexpr int B_WORDS = 3 * B_PLANE;
   constexpr int A_WORDS =
       3 * A_PLANE > (NW / 2) * EPI_REGION ? 3 * A_PLANE : (NW / 2) * EPI_REGION;
   __shared__ __attribute__((aligned(16))) uint32_t As0[A_WORDS];
   __shared__ __attribute__((aligned(16))) uint32_t As1[A_WORDS];
   __shared__ __attribute__((aligned(16))) uint32_t Bs0[B_WORDS];
   __shared__ __attribute__((aligned(16))) uint32_t Bs1[B_WORDS];
-  static_assert(BD || NW == 8 || 3 * B_PLANE >= 2 * EPI_REGION, "epilogue regions");
+  static_assert(NW == 8 || 3 * B_PLANE >= 2 * EPI_REGION, "epilogue regions");
   // Two blocks share each CU, and the wavefront arbiter favours the older
   // one: a block of the first dispatch round (every CU receives one before
   // any receives a second) ran ahead of its CU-mate by ~16 us over a 64-stage
   // tile, and the later block then finished alone at half occupancy.  The
-  // second-round block takes the higher priority instead: for all of its
-  // stages when B comes pre-split, for its first 60 % of stages otherwise
-  // (the settings that measured fastest; the two then end within ~2 us of
-  // each other).  Priority changes timing only, never results.
+  // second-round block takes the higher priority instead, for its first 60 %
+  // of stages (the setting that measured fastest; the two then end within
+  // ~2 us of each other).  Priority changes timing only, never results.
   const bool second_round = blockIdx.x >= NUM_CU;
 
   const int tid = threadIdx.x;
@@ -1062,7 +1059,7 @@ __global__ __launch_bounds__(NW * 64, NW / 2) void gemm_split_kernel(GemmKArgs g
     const int kbeg = (int)(it - (int64_t)t * g.ktiles);
     const int kend = (int)min<int64_t>(g.ktiles, hi - (int64_t)t * g.ktiles);
     it = (int64_t)t * g.ktiles + kend;
-    const TileInfo ti = tile_info(g, t);
+    const TileInfo ti = tile_info(g, t, BN);
     const GemmProblem& P = ti.pi ? g.p[1] : g.p[0];
     const int N = P.N;
     const int m0 = ti.m0, n0 = ti.n0;
@@ -1074,19 +1071,14 @@ __global__ __launch_bounds__(NW * 64, NW / 2) void gemm_split_kernel(GemmKArgs g
     const int64_t lda0 = P.seg[0].lda, lda1 = P.seg[1].lda;
     const int64_t ldb0 = P.seg[0].ldb, ldb1 = P.seg[1].ldb;
     const int K0 = P.seg[0].K, K1 = P.seg[1].K;
-    const uint32_t* const Bq0 = P.seg[0].Bp;
-    const uint32_t* const Bq1 = P.seg[1].Bp;
-    const int64_t bps0 = P.seg[0].bp_plane, bps1 = P.seg[1].bp_plane;
     const bool a_in = va && m0 + BM <= M;
-    const bool b_in = (BD || vb) && n0 + BN <= N;
+    const bool b_in = vb && n0 + BN <= N;
     // KC: thread owns rows x = (tid >> 2) + 64 p (p = 0, 1), k = 4 (tid & 3)
     // .. + 3 (4 lanes per 64-byte row segment).
-    // XC: thread owns k pair kp = tid >> 5 (rows 2 kp and 2 kp + 1) and
-    // x = 4 (tid & 31) .. + 3 (a wavefront reads 2 whole 512-byte rows).
+    // XC: thread owns row k = (tid >> 5) + 8 p, x = 4 (tid & 31) .. + 3 (a
+    // wavefront reads 2 whole 512-byte rows).
     const int kx = tid >> 2, ky = 4 * (tid & 3);
-    // XC: 4 wavefronts: k pair xk of 4 columns xy..xy+3; 8: of 2 columns
-    const int xk = NW == 8 ? tid >> 6 : tid >> 5;
-    const int xy = NW == 8 ? 2 * (tid & 63) : 4 * (tid & 31);
+    const int xk = tid >> 5, xy = 4 * (tid & 31);
 
     float4 ra[2], rb[2];
     auto load_op = [&](float4 (&r)[2], bool kc, const float* X, int64_t ld,
@@ -1097,28 +1089,11 @@ __global__ __launch_bounds__(NW * 64, NW / 2) void gemm_split_kernel(GemmKArgs g
           const int x = x0 + kx + 64 * p, k = k0 + ky;
           r[p] = fast ? ld4(X + (int64_t)x * ld + k) : load4(X, ld, x, k, X_extent, K, vec);
         }
-      } else if (NW == 8) {  // two columns of rows k, k + 1 in .x, .y
-        const int k = k0 + 2 * xk, x = x0 + xy;
-        float2 u0, u1;
-        if (fast) {
-          const float* q = X + (int64_t)k * ld + x;
-          u0 = *reinterpret_cast<const float2*>(q);
-          u1 = *reinterpret_cast<const float2*>(q + ld);
-        } else {
-          u0 = load2(X, ld, k, x, K, X_extent, vec);
-          u1 = load2(X, ld, k + 1, x, K, X_extent, vec);
-        }
-        r[0] = make_float4(u0.x, u0.y, 0.f, 0.f);
-        r[1] = make_float4(u1.x, u1.y, 0.f, 0.f);
       } else {
-        const int k = k0 + 2 * xk, x = x0 + xy;
-        if (fast) {
-          const float* q = X + (int64_t)k * ld + x;
-          r[0] = ld4(q);
-          r[1] = ld4(q + ld);
-        } else {
-          r[0] = load4(X, ld, k, x, K, X_extent, vec);
-          r[1] = load4(X, ld, k + 1, x, K, X_extent, vec);
+#pragma unroll
+        for (int p = 0; p < AP; ++p) {
+          const int k = k0 + xk + 8 * p, x = x0 + xy;
+          r[p] = fast ? ld4(X + (int64_t)k * ld + x) : load4(X, ld, k, x, K, X_extent, vec);
         }
       }
     };
@@ -1128,40 +1103,20 @@ __global__ __launch_bounds__(NW * 64, NW / 2) void gemm_split_kernel(GemmKArgs g
       const int k0 = (s1 ? ks - kt0 : ks) * BKS;
       const bool fk = k0 + BKS <= K;
       load_op(ra, A_KC, s1 ? A1p : A0p, s1 ? lda1 : lda0, m0, M, k0, K, a_in && fk, va);
-      if (!BD)
-        load_op(rb, B_KC, s1 ? B1p : B0p, s1 ? ldb1 : ldb0, n0, N, k0, K, b_in && fk, vb);
+      load_op(rb, B_KC, s1 ? B1p : B0p, s1 ? ldb1 : ldb0, n0, N, k0, K, b_in && fk, vb);
     };
     // Split this thread's values and write the three pieces.
     auto store_op = [&](uint32_t* L, const float4 (&r)[2], bool kc, int plane) {
-      if (kc) {  // 4 consecutive k of rows x and x + 64
+      // four consecutive k of row x + 64 p, or four consecutive x of row k + 8 p
 #pragma unroll
-        for (int p = 0; p < AP; ++p) {
-          uint2 h, m, l;
-          split3(r[p].x, r[p].y, h.x, m.x, l.x);
-          split3(r[p].z, r[p].w, h.y, m.y, l.y);
-          const int w = (kx + 64 * p) * KCS_ROW + ky / 2;
-          *reinterpret_cast<uint2*>(&L[w]) = h;
-          *reinterpret_cast<uint2*>(&L[plane + w]) = m;
-          *reinterpret_cast<uint2*>(&L[2 * plane + w]) = l;
-        }
-      } else if (NW == 8) {  // k pair (rows 2kp, 2kp + 1) of 2 consecutive x
+      for (int p = 0; p < AP; ++p) {
         uint2 h, m, l;
-        split3(r[0].x, r[1].x, h.x, m.x, l.x);
-        split3(r[0].y, r[1].y, h.y, m.y, l.y);
-        const int w = xcs_word(xk, xy);
+        split3(r[p].x, r[p].y, h.x, m.x, l.x);
+        split3(r[p].z, r[p].w, h.y, m.y, l.y);
+        const int w = kc ? (kx + 64 * p) * KCS_ROW + ky / 2 : xcs_word(xk + 8 * p, xy);
         *reinterpret_cast<uint2*>(&L[w]) = h;
         *reinterpret_cast<uint2*>(&L[plane + w]) = m;
         *reinterpret_cast<uint2*>(&L[2 * plane + w]) = l;
-      } else {   // k pair (rows 2kp, 2kp + 1) of 4 consecutive x
-        uint4 h, m, l;
-        split3(r[0].x, r[1].x, h.x, m.x, l.x);
-        split3(r[0].y, r[1].y, h.y, m.y, l.y);
-        split3(r[0].z, r[1].z, h.z, m.z, l.z);
-        split3(r[0].w, r[1].w, h.w, m.w, l.w);
-        const int w = xcs_word(xk, xy);
-        *reinterpret_cast<uint4*>(&L[w]) = h;
-        *reinterpret_cast<uint4*>(&L[plane + w]) = m;
-        *reinterpret_cast<uint4*>(&L[2 * plane + w]) = l;
       }
     };
 
@@ -1175,37 +1130,17 @@ __global__ __launch_bounds__(NW * 64, NW / 2) void gemm_split_kernel(GemmKArgs g
 
     // fragment of block i from one piece plane
     auto frag = [&](const uint32_t* L, bool kc, int wbase, int i) {
-      uint4 w;
-      const int x = wbase + i * 32 + lr;
       if (kc) {
-        w = *reinterpret_cast<const uint4*>(&L[x * KCS_ROW + 4 * lh]);
-      } else {
-        w.x = L[xcs_word(4 * lh + 0, x)];
-        w.y = L[xcs_word(4 * lh + 1, x)];
-        w.z = L[xcs_word(4 * lh + 2, x)];
-        w.w = L[xcs_word(4 * lh + 3, x)];
+        const int x = wbase + i * 32 + lr;
+        return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&L[x * KCS_ROW + 4 * lh]));
       }
-      return __builtin_bit_cast(bf16x8, w);
-    };
-    typedef bf16x8 BFr[3][NJ];
-    // B fragments of stage ks from the planes (BD); columns past N read as
-    // zeros unless `full` (the tile's columns all lie inside N)
-    auto load_bfr = [&](BFr& bf, int ks, bool full) {
-      const bool s1 = ks >= kt0;
-      const uint32_t* Bq = s1 ? Bq1 : Bq0;
-      const int64_t ps = s1 ? bps1 : bps0;
-      const int64_t gN = (int64_t)(s1 ? ks - kt0 : ks) * N;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int n = n0 + wn * 32 * NJ + j * 32 + lr;
-        const uint32_t* src = Bq + (gN + n) * 8 + 4 * lh;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-          uint4 w = make_uint4(0u, 0u, 0u, 0u);
-          if (full || n < N) w = *reinterpret_cast<const uint4*>(src + q * ps);
-          bf[q][j] = __builtin_bit_cast(bf16x8, w);
-        }
-      }
+      // rows k = 8 lh .. + 3 and + 4 .. + 7 of the lane's 16 columns
+      const uint32_t* q = &L[xcs_word(8 * lh + ((lane & 15) >> 2),
+                                      wbase + i * 32 + (lr & 16) + 4 * (lane & 3))];
+      struct {
+        s16x4 lo, hi;
+      } v = {lds_read_tr(q), lds_read_tr(q + 32)};
+      return __builtin_bit_cast(bf16x8, v);
     };
     // The six piece products down to 2^-16 of hi x hi, smallest first; what
     // is left out (mid lo + lo mid + lo lo) is below 2^-24 of |a b|.
@@ -1254,69 +1189,34 @@ __global__ __launch_bounds__(NW * 64, NW / 2) void gemm_split_kernel(GemmKArgs g
         const bool s1 = ks >= kt0;
         const int k0 = (s1 ? ks - kt0 : ks) * BKS;
         load_op(ra, A_KC, s1 ? A1p : A0p, s1 ? lda1 : lda0, m0, M, k0, 0, true, true);
-        if (!BD)
-          load_op(rb, B_KC, s1 ? B1p : B0p, s1 ? ldb1 : ldb0, n0, N, k0, 0, true, true);
+        load_op(rb, B_KC, s1 ? B1p : B0p, s1 ? ldb1 : ldb0, n0, N, k0, 0, true, true);
       };
-      if (BD) {
-        // A through LDS as below; B fragments of stage k + 1 loaded while
-        // stage k's products run (two register sets, alternating)
-        BFr b0, b1;
-        auto step = [&](const uint32_t* as, uint32_t* as_n, int kl, BFr& bcur,
-                        BFr& bnext, int kb) {
-          if (second_round)
-            __builtin_amdgcn_s_setprio(1);
-          else
-            __builtin_amdgcn_s_setprio(0);
-          Frags f;
-          read_a(f, as);
-#pragma unroll
-          for (int q = 0; q < 3; ++q)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) f.b[q][j] = bcur[q][j];
-          store_op(as_n, ra, A_KC, A_PLANE);
-          load_full(kl);
-          load_bfr(bnext, min(kb, kf - 1), true);
-          products(f);
-          __syncthreads();
-        };
-        load_full(kbeg);
-        store_op(As0, ra, A_KC, A_PLANE);
-        load_full(kbeg + 1);
-        load_bfr(b0, kbeg, true);
+      // Read this stage's fragments, split and store the next stage (in
+      // registers) into the other LDS buffer, issue the loads of the stage
+      // after it, the products, one barrier.  The fragment reads go first
+      // so that the next stage's LDS writes do not hold them up.
+      auto step = [&](const uint32_t* as, const uint32_t* bs, uint32_t* as_n,
+                      uint32_t* bs_n, int kl) {
+        if (second_round && (kl - kbeg) * 10 < (kf - kbeg) * 6)
+          __builtin_amdgcn_s_setprio(1);
+        else
+          __builtin_amdgcn_s_setprio(0);
+        const Frags f = read_frags(as, bs);
+        store_op(as_n, ra, A_KC, A_PLANE);
+        store_op(bs_n, rb, B_KC, B_PLANE);
+        load_full(kl);
+        products(f);
         __syncthreads();
-        for (int k = kbeg; k < kf; k += 2) {
-          step(As0, As1, k + 2, b0, b1, k + 1);
-          if (k + 1 >= kf) break;
-          step(As1, As0, k + 3, b1, b0, k + 2);
-        }
-      } else {
-        // Read this stage's fragments, split and store the next stage (in
-        // registers) into the other LDS buffer, issue the loads of the stage
-        // after it, the products, one barrier.  The fragment reads go first
-        // so that the next stage's LDS writes do not hold them up.
-        auto step = [&](const uint32_t* as, const uint32_t* bs, uint32_t* as_n,
-                        uint32_t* bs_n, int kl) {
-          if (second_round && (kl - kbeg) * 10 < (kf - kbeg) * 6)
-            __builtin_amdgcn_s_setprio(1);
-          else
-            __builtin_amdgcn_s_setprio(0);
-          const Frags f = read_frags(as, bs);
-          store_op(as_n, ra, A_KC, A_PLANE);
-          store_op(bs_n, rb, B_KC, B_PLANE);
-          load_full(kl);
-          products(f);
-          __syncthreads();
-        };
-        load_full(kbeg);
-        store_op(As0, ra, A_KC, A_PLANE);
-        store_op(Bs0, rb, B_KC, B_PLANE);
-        load_full(kbeg + 1);
-        __syncthreads();
-        for (int k = kbeg; k < kf; k += 2) {
-          step(As0, Bs0, As1, Bs1, k + 2);
-          if (k + 1 >= kf) break;
-          step(As1, Bs1, As0, Bs0, k + 3);
-        }
+      };
+      load_full(kbeg);
+      store_op(As0, ra, A_KC, A_PLANE);
+      store_op(Bs0, rb, B_KC, B_PLANE);
+      load_full(kbeg + 1);
+      __syncthreads();
+      for (int k = kbeg; k < kf; k += 2) {
+        step(As0, Bs0, As1, Bs1, k + 2);
+        if (k + 1 >= kf) break;
+        step(As1, Bs1, As0, Bs0, k + 3);
       }
     }
 
@@ -1329,17 +1229,10 @@ __global__ __launch_bounds__(NW * 64, NW / 2) void gemm_split_kernel(GemmKArgs g
         uint32_t* as = buf ? As1 : As0;
         uint32_t* bs = buf ? Bs1 : Bs0;
         store_op(as, ra, A_KC, A_PLANE);
-        if (!BD) store_op(bs, rb, B_KC, B_PLANE);
+        store_op(bs, rb, B_KC, B_PLANE);
         __syncthreads();
         if (ks + 1 < kend) load_slice(ks + 1);
-        if (BD) {
-          Frags f;
-          read_a(f, as);
-          load_bfr(f.b, ks, false);
-          products(f);
-        } else {
-          products(read_frags(as, bs));
-        }
+        products(read_frags(as, bs));
         buf ^= 1;
       }
       __syncthreads();
@@ -1351,64 +1244,507 @@ __global__ __launch_bounds__(NW * 64, NW / 2) void gemm_split_kernel(GemmKArgs g
                                (BM * BN);
     store_acc<NJ, NW / 2>(P, ti, M, acc, whole, part, wm, wn, lr, lh,
                           g.vec_c[ti.pi] != 0, reinterpret_cast<float*>(As0),
-                          reinterpret_cast<float*>(BD || NW == 8 ? As1 : Bs0));
+                          reinterpret_cast<float*>(NW == 8 ? As1 : Bs0));
   }
 }
 
-// One thread per word (bf16 pair k, k + 1 of one column) of the planes;
-// blockIdx.y picks the matrix (job) of the launch.
+// ------------------------------------- split products, B pieces given
+//
+// The split-product kernel of the launches whose B comes as ready pieces
+// (GemmSeg::Bp): forward products and input gradients.  What bounds these
+// launches is power: with random operands the matrix cores sustain 1,860
+// TFLOP/s of 32 x 32 x 16 bf16 MFMAs and 2,110 of 16 x 16 x 32 ones
+// (register operands only; 2,470 of either with constant operands), so this
+// kernel multiplies with the latter, 32 k per stage.
+// Lane group g = lane / 16 supplies k = 8 g + j (j = 0..7) in both operands.
+//   A K-contiguous: LDS plane [x][k] rows of 16 words (k pairs) + 4 words of
+//     padding (80 bytes: eight consecutive rows of a 128-bit fragment read
+//     fall on distinct banks); a fragment is one 128-bit read.
+//   A X-contiguous: planes of 16-column panels, [x / 16][k][x % 16] bf16
+//     (rows of 32 bytes; panels 8 words apart in bank, so that the panels of
+//     a row's stores use different banks); a fragment is two transposing
+//     64-bit reads (ds_read_tr16_b64: among 16 lanes, lane l gets column l
+//     of the four 32-byte rows that lanes 0-3, 4-7, 8-11, 12-15 address).
+//   B: fragments straight from the planes in global memory (two runs of 512
+//     consecutive bytes each), one stage ahead.
+// Four wavefronts per block, each 64 x 16 NJ of the 128 x 32 NJ tile.
+// Measured (8000 x 1024, K = 1024 / 608; 50000 x 1024, K = 2048), against
+// eight wavefronts of 32 x 32 x 16 MFMAs, 16 k per stage: 89 / 56 / 1,082 us,
+// before 95 / 59 / 1,127.  At K = 4096 the shader clock rises from 1.68 to
+// 1.98 GHz for the same work.
+constexpr int BKP = 32;
+constexpr int KCP_ROW = 20;
+constexpr int KCP_PLANE = 128 * KCP_ROW;
+constexpr int XCP_PANEL = BKP * 8 + 8;  // words
+constexpr int XCP_PLANE = 8 * XCP_PANEL;
+
+// Word of element (k, x) (x even) of an x-contiguous plane.
+__device__ inline int xcp_word(int k, int x) {
+  return (x >> 4) * XCP_PANEL + k * 8 + ((x & 15) >> 1);
+}
+
+// 16 bytes at base + voff + soff: a uniform base and a 32-bit offset per lane,
+// so that the loads of a whole stage need two address registers.
+__device__ inline uint4 load16(const void* base, uint32_t voff, uint32_t soff) {
+#ifdef __HIP_DEVICE_COMPILE__
+  const __amdgpu_buffer_rsrc_t r =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, -1, 0x00020000);
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+#else
+  return uint4{};
+#endif
+}
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// store_acc for 16 x 16 MFMA blocks (lane l, register r: row 4 (l / 16) + r,
+// column l % 16): wavefront (wm, wn) holds 4 x NJ of them.  Interior tiles
+// with float4 rows go through LDS 16 rows at a time, each wavefront in its
+// own region of `lds` (rows of 16 NJ + 4 floats: the four row groups of a
+// store alternate between two bank halves), and are stored as whole rows.
+template <int NJ>
+__device__ inline void store_acc16(const GemmProblem& P, const TileInfo& ti, int M,
+                                   const floatx4 (&acc)[4][NJ], bool whole, float* part,
+                                   int wm, int wn, int lane, bool vec_c, float* lds) {
+  constexpr int BNT = 32 * NJ, ROW = 16 * NJ + 4;
+  const int N = P.N, lr = lane & 15, lg = lane >> 4;
+  // moved-back tiles take the guarded path, which skips what they do not own
+  const bool interior = ti.m0 + BM <= M && ti.n0 + BNT <= N && ti.m0 == ti.r0 &&
+                        ti.n0 == ti.c0;
+  if (whole && interior && vec_c) {
+    float* L = lds + (2 * wn + wm) * 16 * ROW;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) L[(4 * lg + r) * ROW + 16 * j + lr] = acc[i][j][r];
+#pragma unroll
+      for (int q = 0; q < NJ; ++q) {
+        const int e = q * 64 + lane;
+        const int rl = e / (4 * NJ), cl = 4 * (e % (4 * NJ));
+        const int row = ti.m0 + wm * 64 + i * 16 + rl, col = ti.n0 + wn * 16 * NJ + cl;
+        float4 v = ld4(&L[rl * ROW + cl]);
+        if (P.bias) {
+          const float4 bc = ld4(P.bias + col);
+          v.x += bc.x; v.y += bc.y; v.z += bc.z; v.w += bc.w;
+        }
+        if (P.relu) {
+          v.x = fmaxf(v.x, 0.f); v.y = fmaxf(v.y, 0.f);
+          v.z = fmaxf(v.z, 0.f); v.w = fmaxf(v.w, 0.f);
+        }
+        if (P.mask) {
+          const float4 m = ld4(P.mask + (int64_t)row * P.ld_mask + col);
+          if (!(m.x > 0.f)) v.x = 0.f;
+          if (!(m.y > 0.f)) v.y = 0.f;
+          if (!(m.z > 0.f)) v.z = 0.f;
+          if (!(m.w > 0.f)) v.w = 0.f;
+        }
+        *reinterpret_cast<float4*>(P.C + (int64_t)row * P.ldc + col) = v;
+      }
+    }
+    __syncthreads();
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int rl = wm * 64 + i * 16 + 4 * lg, cl = wn * 16 * NJ + j * 16 + lr;
+      const int row0 = ti.m0 + rl, col = ti.n0 + cl;
+      if (!whole) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[(rl + r) * BNT + cl] = acc[i][j][r];
+        continue;
+      }
+      if (col >= N || col < ti.c0) continue;
+      const float bc = P.bias ? P.bias[col] : 0.f;
+      float mv[4];
+      if (P.mask) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          mv[r] = row0 + r < M ? P.mask[(int64_t)(row0 + r) * P.ld_mask + col] : 0.f;
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = row0 + r;
+        if (row >= M || row < ti.r0) continue;
+        float v = acc[i][j][r] + bc;
+        if (P.relu) v = fmaxf(v, 0.f);
+        if (P.mask && !(mv[r] > 0.f)) v = 0.f;
+        P.C[(int64_t)row * P.ldc + col] = v;
+      }
+    }
+}
+
+// CHAIN: each stage's products are summed from zero and added to the running
+// sum by a rounding fp32 addition.  The matrix cores truncate what they shift
+// out when they add to a larger accumulator; so the error of one long sum
+// stays below that of the partial sums of a split one (K = 1024: 1.2e-7 of
+// |C|, 2.4e-7 in four parts, 4.9e-7 in one without this).  The additions cost
+// 3 % where a block has its CU to itself, 20 % where two share one.
+template <bool AT, int NJ, bool CHAIN>
+__global__ __launch_bounds__(256, 2) void gemm_planes_kernel(GemmKArgs g, GemmKArgs fx) {
+  if (run_pending_fixup(g, fx)) return;
+  constexpr int BNT = 32 * NJ;
+  constexpr bool A_KC = !AT;
+  constexpr int A_PLANE = A_KC ? KCP_PLANE : XCP_PLANE;
+  __shared__ __attribute__((aligned(16))) uint32_t As0[3 * A_PLANE];
+  __shared__ __attribute__((aligned(16))) uint32_t As1[3 * A_PLANE];
+  static_assert(3 * A_PLANE >= 4 * 16 * (16 * NJ + 4), "epilogue regions");
+  // Two blocks share a CU, and the wavefront arbiter favours the older one,
+  // which would run ahead and leave the later one to finish alone at half
+  // occupancy: the second-round block takes the higher priority (timing only).
+  if (blockIdx.x >= NUM_CU) __builtin_amdgcn_s_setprio(1);
+
+  const int tid = threadIdx.x;
+  const int wave = tid >> 6, lane = tid & 63;
+  const int wm = wave & 1, wn = wave >> 1;
+  const int lr = lane & 15, lg = lane >> 4;
+  const int M = g.M;
+
+  const int lb = logical_block(blockIdx.x, g.nblocks);
+  int64_t lo, hi;
+  if (g.splits > 1) {
+    const int sp = lb / g.tiles, t = lb % g.tiles;
+    lo = (int64_t)t * g.ktiles + (int64_t)sp * g.ktiles / g.splits;
+    hi = (int64_t)t * g.ktiles + (int64_t)(sp + 1) * g.ktiles / g.splits;
+  } else {
+    lo = block_lo(lb, g.iters, g.nblocks);
+    hi = block_lo(lb + 1, g.iters, g.nblocks);
+  }
+
+  int seg = 0;
+  for (int64_t it = lo; it < hi; ++seg) {
+    const int t = (int)(it / g.ktiles);
+    const int kbeg = (int)(it - (int64_t)t * g.ktiles);
+    const int kend = (int)min<int64_t>(g.ktiles, hi - (int64_t)t * g.ktiles);
+    it = (int64_t)t * g.ktiles + kend;
+    const TileInfo ti = tile_info(g, t, BNT);
+    const GemmProblem& P = ti.pi ? g.p[1] : g.p[0];
+    const int N = P.N;
+    const int m0 = ti.m0, n0 = ti.n0;
+    const int kt0 = ti.pi ? g.ktiles0[1] : g.ktiles0[0];
+    const float* const A0p = P.seg[0].A;
+    const float* const A1p = P.seg[1].A;
+    const int64_t lda0 = P.seg[0].lda, lda1 = P.seg[1].lda;
+    const int K0 = P.seg[0].K, K1 = P.seg[1].K;
+    const uint32_t* const Bq0 = P.seg[0].Bp;
+    const uint32_t* const Bq1 = P.seg[1].Bp;
+    const int64_t bps0 = P.seg[0].bp_plane, bps1 = P.seg[1].bp_plane;
+    const bool va = g.vec_a != 0;
+    // KC: thread owns k = 4 (tid & 7) .. + 3 of rows x = (tid >> 3) + 32 p
+    // (8 lanes per 128-byte row segment).
+    // XC: thread owns x = 4 (tid & 31) .. + 3 of rows k = (tid >> 5) + 8 p
+    // (a wavefront reads 2 whole 512-byte rows).
+    const int ax = A_KC ? tid >> 3 : tid >> 5;
+    const int ay = A_KC ? 4 * (tid & 7) : 4 * (tid & 31);
+    constexpr int ASTEP = A_KC ? 32 : 8;
+
+    typedef float4 Raw[4];
+    // Any stage: guarded loads, zeros outside the operand.
+    auto load_slice = [&](Raw& r, int ks) {
+      const bool s1 = ks >= kt0;
+      const int K = s1 ? K1 : K0;
+      const int k0 = (s1 ? ks - kt0 : ks) * BKP;
+      const float* A = s1 ? A1p : A0p;
+      const int64_t lda = s1 ? lda1 : lda0;
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+        r[p] = A_KC ? load4(A, lda, m0 + ax + ASTEP * p, k0 + ay, M, K, va)
+                    : load4(A, lda, k0 + ax + ASTEP * p, m0 + ay, K, M, va);
+    };
+    // Split this thread's values and write the three pieces.
+    auto store_op = [&](uint32_t* L, const Raw& r) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        uint2 h, m, l;
+        split3(r[p].x, r[p].y, h.x, m.x, l.x);
+        split3(r[p].z, r[p].w, h.y, m.y, l.y);
+        const int w = A_KC ? (ax + ASTEP * p) * KCP_ROW + ay / 2 : xcp_word(ax + ASTEP * p, ay);
+        *reinterpret_cast<uint2*>(&L[w]) = h;
+        *reinterpret_cast<uint2*>(&L[A_PLANE + w]) = m;
+        *reinterpret_cast<uint2*>(&L[2 * A_PLANE + w]) = l;
+      }
+    };
+
+    floatx4 acc[4][NJ];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+
+    typedef bf16x8 AFr[3][4];
+    typedef bf16x8 BFr[3][NJ];
+    auto read_a = [&](AFr& f, const uint32_t* L) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (A_KC) {
+            const int x = wm * 64 + i * 16 + lr;
+            f[q][i] = __builtin_bit_cast(
+                bf16x8, *reinterpret_cast<const uint4*>(&L[q * A_PLANE + x * KCP_ROW + 4 * lg]));
+          } else {  // rows k = 8 lg .. + 3 and + 4 .. + 7 of the block's 16 columns
+            const uint32_t* s =
+                &L[q * A_PLANE + xcp_word(8 * lg + (lr >> 2), wm * 64 + i * 16 + 4 * (lr & 3))];
+            struct {
+              s16x4 lo, hi;
+            } v = {lds_read_tr(s), lds_read_tr(s + 32)};
+            f[q][i] = __builtin_bit_cast(bf16x8, v);
+          }
+        }
+    };
+    // B fragments of stage ks; `full`: its 32 k all lie inside B, otherwise
+    // the last 16-deep group may be missing and reads as zeros.  Columns past
+    // N repeat the last one (their results are not stored).
+    uint32_t bv[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+      bv[j] = ((uint32_t)(lg >> 1) * N + min(wn * 16 * NJ + j * 16 + lr, N - 1 - n0)) * 32 +
+              16 * (lg & 1);
+    auto load_b = [&](BFr& f, int ks, bool full) {
+      const bool s1 = ks >= kt0;
+      const int g0 = 2 * (s1 ? ks - kt0 : ks);  // 16-deep groups
+      const bool ok = full || (int64_t)(g0 + (lg >> 1)) * 16 < (s1 ? K1 : K0);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const uint32_t* base =
+            (s1 ? Bq1 : Bq0) + q * (s1 ? bps1 : bps0) + ((int64_t)g0 * N + n0) * 8;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          uint4 w = make_uint4(0u, 0u, 0u, 0u);
+          if (ok) w = load16(base, bv[j], 0);
+          f[q][j] = __builtin_bit_cast(bf16x8, w);
+        }
+      }
+    };
+    // The six piece products down to 2^-16 of hi x hi, smallest first; what
+    // is left out (mid lo + lo mid + lo lo) is below 2^-24 of |a b|.
+    auto products = [&](const AFr& a, const BFr& b) {
+      constexpr int terms[6][2] = {{1, 1}, {2, 0}, {0, 2}, {1, 0}, {0, 1}, {0, 0}};
+      if constexpr (CHAIN) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          floatx4 t[4];
+#pragma unroll
+          for (int u = 0; u < 6; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              t[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  a[terms[u][0]][i], b[terms[u][1]][j],
+                  u == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : t[i], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[i][j] += t[i];
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < 6; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  a[terms[u][0]][i], b[terms[u][1]][j], acc[i][j], 0, 0, 0);
+      }
+    };
+
+    // Stages [kbeg, kf) are full: pipelined path, no guards (rows past M
+    // repeat the last one; loads past the end repeat the last stage, never
+    // used).
+    int kf = kbeg;
+    if (va && (A_KC || m0 + BM <= M)) {
+      const int f0 = K0 / BKP, e1 = kt0 + K1 / BKP;
+      if (kbeg < f0)
+        kf = min(kend, f0 == kt0 ? e1 : f0);
+      else if (kbeg >= kt0 && kbeg < e1)
+        kf = min(kend, e1);
+    }
+    if (kf > kbeg) {
+      auto load_full = [&](Raw& r, int ks) {
+        ks = min(ks, kf - 1);
+        const bool s1 = ks >= kt0;
+        const int k0 = (s1 ? ks - kt0 : ks) * BKP;
+        const float* A = s1 ? A1p : A0p;
+        const int64_t lda = s1 ? lda1 : lda0;
+        const float* base = A_KC ? A + (int64_t)m0 * lda + k0 : A + (int64_t)k0 * lda + m0;
+        const uint32_t ldb = (uint32_t)lda * 4;  // below 2^25: vec_a
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const int x = A_KC ? min(ax + ASTEP * p, M - 1 - m0) : ax + ASTEP * p;
+          r[p] = __builtin_bit_cast(float4, load16(base, x * ldb + ay * 4, 0));
+        }
+      };
+      BFr b0, b1;
+      Raw r;
+      auto step = [&](int k, const uint32_t* as, uint32_t* as_n, const BFr& bc, BFr& bn) {
+        AFr a;
+        __syncthreads();  // stage k stored; stage k - 1's fragments all read
+        read_a(a, as);
+        store_op(as_n, r);  // stage k + 1
+        load_full(r, k + 2);
+        load_b(bn, min(k + 1, kf - 1), true);
+        products(a, bc);
+      };
+      load_full(r, kbeg);
+      load_b(b0, kbeg, true);
+      store_op(As0, r);
+      load_full(r, kbeg + 1);
+      for (int k = kbeg; k < kf; k += 2) {
+        step(k, As0, As1, b0, b1);
+        if (k + 1 >= kf) break;
+        step(k + 1, As1, As0, b1, b0);
+      }
+      __syncthreads();
+    }
+
+    // Remaining stages (partial K; unaligned rows): guarded loads, one stage
+    // in registers ahead.
+    if (kf < kend) {
+      Raw r;
+      load_slice(r, kf);
+      for (int ks = kf; ks < kend; ++ks) {
+        AFr a;
+        BFr b;
+        load_b(b, ks, false);
+        store_op(As0, r);
+        __syncthreads();
+        if (ks + 1 < kend) load_slice(r, ks + 1);
+        read_a(a, As0);
+        products(a, b);
+        __syncthreads();
+      }
+    }
+
+    const bool whole = kbeg == 0 && kend == g.ktiles;
+    float* part = g.part + (g.splits > 1 ? (int64_t)lb
+                                         : (int64_t)lb * 2 + (seg > 0 ? 1 : 0)) *
+                               (BM * BNT);
+    store_acc16<NJ>(P, ti, M, acc, whole, part, wm, wn, lane, g.vec_c[ti.pi] != 0,
+                    reinterpret_cast<float*>(As0));
+  }
+}
+
+// One thread per word (bf16 pair k, k + 1 of one column) of the planes: a
+// block takes 32 columns of one 16-deep group (blockIdx.x, .y) of matrix
+// blockIdx.z.  A K x N matrix is read as rows of 32 columns and handed over
+// through LDS; an N x K one holds each thread's pair side by side.
 struct SplitJobs {
   SplitJob j[MAX_SPLIT_JOBS];
   int64_t pw[MAX_SPLIT_JOBS];  // words of one plane of job i
 };
-__global__ __launch_bounds__(256) void split_b_planes_kernel(SplitJobs jobs) {
-  const SplitJob& J = jobs.j[blockIdx.y];
-  const int64_t plane_words = jobs.pw[blockIdx.y];
-  const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (w >= plane_words) return;
+__global__ __launch_bounds__(256) void split_b_planes_kernel(SplitJobs jobs, int y0) {
+  const SplitJob& J = jobs.j[blockIdx.z];
   const float* __restrict__ B = J.B;
-  uint32_t* __restrict__ planes = J.planes;
   const int K = J.K, N = J.N;
   const int64_t ld = J.ld;
-  const bool kn = !J.trans_b;
-  const int tp = (int)(w & 7);
-  const int64_t gn = w >> 3;
-  const int n = (int)(gn % N), gi = (int)(gn / N);
-  const int k = 16 * gi + 2 * tp;
-  auto at = [&](int kk) -> float {
-    if (kk >= K) return 0.f;
-    return kn ? B[(int64_t)kk * ld + n] : B[(int64_t)n * ld + kk];
-  };
+  const int64_t g = (int64_t)y0 + blockIdx.y;  // 16-deep group
+  const int n0 = 32 * blockIdx.x, tid = threadIdx.x;
+  if (g * 16 >= K || n0 >= N) return;  // the grid covers the largest job
+  const int k0 = 16 * (int)g;
+  const int n = n0 + (tid >> 3), tp = tid & 7;
+  float x0 = 0.f, x1 = 0.f;
+  if (J.trans_b) {
+    const int k = k0 + 2 * tp;
+    if (n < N) {
+      const float* p = B + (int64_t)n * ld + k;
+      if (k < K) x0 = p[0];
+      if (k + 1 < K) x1 = p[1];
+    }
+  } else {
+    __shared__ float t[16][33];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int kl = 8 * r + (tid >> 5), nl = tid & 31;
+      t[kl][nl] = k0 + kl < K && n0 + nl < N ? B[(int64_t)(k0 + kl) * ld + n0 + nl] : 0.f;
+    }
+    __syncthreads();
+    x0 = t[2 * tp][tid >> 3];
+    x1 = t[2 * tp + 1][tid >> 3];
+  }
+  if (n >= N) return;
   uint32_t h, m, l;
-  split3(at(k), at(k + 1), h, m, l);
-  planes[w] = h;
-  planes[plane_words + w] = m;
-  planes[2 * plane_words + w] = l;
+  split3(x0, x1, h, m, l);
+  const int64_t plane_words = jobs.pw[blockIdx.z];
+  uint32_t* __restrict__ planes = J.planes + (g * N + n) * 8 + tp;
+  planes[0] = h;
+  planes[plane_words] = m;
+  planes[2 * plane_words] = l;
 }
 
 size_t b_planes_words(int32_t K, int32_t N) {
   if (K <= 0 || N <= 0) return 0;
-  return 3 * (size_t)ceil_div(K, BKS) * (size_t)N * 8;
+  return 3 * (size_t)ceil_div(K, 16) * (size_t)N * 8;
 }
 
 hipError_t split_b_planes_launch(const SplitJob* jobs, int njobs, hipStream_t s) {
   if (njobs < 1 || njobs > MAX_SPLIT_JOBS) return hipErrorInvalidValue;
   SplitJobs a;
   memset(&a, 0, sizeof(a));
-  int64_t pw_max = 0;
   double words = 0;
+  int64_t gx = 0, gy = 0;
   for (int i = 0; i < njobs; ++i) {
     a.j[i] = jobs[i];
-    const int64_t pw = (int64_t)(b_planes_words(jobs[i].K, jobs[i].N) / 3);
-    a.pw[i] = pw;
-    pw_max = std::max(pw_max, pw);
-    words += (double)pw;
+    a.pw[i] = (int64_t)(b_planes_words(jobs[i].K, jobs[i].N) / 3);
+    if (a.pw[i] > 0) {
+      gx = std::max(gx, ceil_div(jobs[i].N, 32));
+      gy = std::max(gy, ceil_div(jobs[i].K, 16));
+    }
+    words += (double)a.pw[i];
   }
-  if (pw_max == 0) return hipSuccess;
+  if (gx == 0) return hipSuccess;
+  // (grid y and z hold 65,535 blocks: deeper matrices go in slabs of k)
   timer_begin(GNN_K_WSPLIT, s);
-  split_b_planes_kernel<<<dim3((unsigned)ceil_div(pw_max, 256), (unsigned)njobs), 256, 0, s>>>(a);
+  for (int64_t y0 = 0; y0 < gy; y0 += 65535)
+    split_b_planes_kernel<<<dim3((unsigned)gx, (unsigned)std::min<int64_t>(gy - y0, 65535),
+                                 (unsigned)njobs),
+                            256, 0, s>>>(a, (int)y0);
   timer_end(GNN_K_WSPLIT, 20.0 * words, s);  // per word: 2 floats in, 3 words out
   return hipGetLastError();
+}
+
+bool gemm_use_planes(int32_t M, int32_t mode) { return mode == GEMM_SPLIT && M >= 512; }
+
+GemmBatch gemm_with_planes(GemmBatch b) {
+  b.b_planes = gemm_use_planes(b.p[0].M, b.mode);
+  return b;
+}
+
+size_t gemm_planes_bytes(const GemmBatch* b, int n) {
+  size_t bytes = 0;
+  for (int i = 0; i < n; ++i)
+    if (b[i].b_planes)
+      for (int k = 0; k < b[i].nprob; ++k)
+        for (int s = 0; s < b[i].p[k].nseg; ++s)
+          bytes += round_up(b_planes_words(b[i].p[k].seg[s].K, b[i].p[k].N) * 4, 256);
+  return bytes;
+}
+
+hipError_t gemm_split_planes(GemmBatch* b, int n, void* planes, hipStream_t s) {
+  SplitJob jobs[MAX_SPLIT_JOBS];
+  int nj = 0;
+  char* at = static_cast<char*>(planes);
+  for (int i = 0; i < n; ++i) {
+    if (!b[i].b_planes) continue;
+    for (int k = 0; k < b[i].nprob; ++k)
+      for (int q = 0; q < b[i].p[k].nseg; ++q) {
+        GemmSeg& sg = b[i].p[k].seg[q];
+        const size_t words = b_planes_words(sg.K, b[i].p[k].N);
+        sg.Bp = reinterpret_cast<const uint32_t*>(at);
+        sg.bp_plane = (int64_t)(words / 3);
+        jobs[nj++] = {sg.B, sg.ldb, sg.K, b[i].p[k].N, b[i].trans_b,
+                      reinterpret_cast<uint32_t*>(at)};
+        at += round_up(words * 4, 256);
+        if (nj == MAX_SPLIT_JOBS) {
+          const hipError_t e = split_b_planes_launch(jobs, nj, s);
+          if (e != hipSuccess) return e;
+          nj = 0;
+        }
+      }
+  }
+  return nj ? split_b_planes_launch(jobs, nj, s) : hipSuccess;
 }
 
 // ------------------------------------------------------------------ host
@@ -1418,12 +1754,19 @@ struct Shape {
   int64_t iters;
   int nblocks;
   int splits;
+  int bn;     // tile width (64, 96 or 128 with planes, else 128)
+  int chain;  // with planes: CHAIN
 };
+
+// K depth of a stage of the batch's kernel.
+static int stage_k(const GemmBatch& b) {
+  return b.mode == GEMM_BF16 ? BK16 : b.mode == GEMM_F32 ? BK : b.b_planes ? BKP : BKS;
+}
 
 static Shape gemm_shape(const GemmBatch& b) {
   Shape s;
   memset(&s, 0, sizeof(s));
-  const int BK = b.mode == GEMM_BF16 ? BK16 : b.mode == GEMM_SPLIT ? BKS : gnnprop::BK;
+  const int BK = stage_k(b);
   const int M = b.p[0].M;
   s.tiles_m = (int)ceil_div(M, BM);
   s.tiles_n0 = (int)ceil_div(b.p[0].N, BN);
@@ -1437,6 +1780,9 @@ static Shape gemm_shape(const GemmBatch& b) {
   }
   s.ktiles = std::max(s.ktiles, 1);
   s.iters = (int64_t)s.tiles * s.ktiles;
+  s.splits = 1;
+  s.bn = BN;
+  if (s.tiles == 0) return s;  // no rows or no columns: nothing to launch
   // One block per tile when the tiles fill the resident slots well enough.
   // Otherwise, with few tiles and a long K (weight gradients, K = n), split
   // K into S ranges, one (tile, range) per block, ordered split-major so that
@@ -1461,12 +1807,11 @@ static Shape gemm_shape(const GemmBatch& b) {
   const int slots = MAX_BLOCKS;
   const int64_t rounds = ceil_div(s.tiles, slots);
   const double fill = (double)s.tiles / (double)(rounds * slots);
-  const int kt32 = b.mode == GEMM_SPLIT ? (s.ktiles + 1) / 2 : s.ktiles;
+  const int kt32 = b.mode == GEMM_SPLIT && !b.b_planes ? (s.ktiles + 1) / 2 : s.ktiles;
   const int64_t iters32 = (int64_t)s.tiles * kt32;
   const bool one_per_cu = s.tiles >= slots * 7 / 16 &&
                           ((s.tiles <= slots / 2 && kt32 <= 40) ||
                            (b.mode != GEMM_F32 && s.tiles <= slots && kt32 <= 64));
-  s.splits = 1;
   if (fill >= 0.85 || one_per_cu ||
       (iters32 <= slots && (s.tiles > slots / 4 || kt32 < 4))) {
     s.nblocks = s.tiles;
@@ -1478,12 +1823,65 @@ static Shape gemm_shape(const GemmBatch& b) {
     // sharing a tile are consecutive and each holds a partial of it
     s.nblocks = (int)std::min<int64_t>(slots, s.iters);
   }
+  if (b.b_planes) {
+    // Tiles of 64, 96 or 128 columns, whole (one block each, two per CU) or
+    // split along K: whichever the measured times of a launch put first.  A
+    // block with a CU-mate takes s2 us per 32-deep stage, one alone s1, and
+    // 8 us besides (launch, first loads, output); a split launch pays its
+    // reduction on top.  Measured (before: 128 columns only): 8000 x 604, K =
+    // 1024: 441 tiles of 96 columns 67 us, 315 of 128 80; 8000 x 256, K =
+    // 608: 252 tiles of 64 26 us, split along K 32 + 10; 20000 x 1024, K =
+    // 200: 1,256 whole tiles 75 us, stream-K 70 + 27.
+    // Where the rule above shares tiles and whole ones are faster, CHAIN
+    // keeps the result as accurate as the partial sums; not beyond 512 tiles,
+    // where few are shared: those stay shared over more than 640 k.
+    const double s1[3] = {0.98, 1.26, 1.5}, s2[3] = {1.4, 1.9, 2.5}, fixed = 8.0;
+    const bool shared = s.nblocks != s.tiles;
+    const bool chain = shared && s.tiles <= slots;
+    if (shared && !chain && s.ktiles > 20) return s;
+    const int parts = s.splits;
+    auto per_stage = [&](int i, int blocks) { return blocks <= NUM_CU ? s1[i] : s2[i]; };
+    auto whole_stage = [&](int i, int blocks) {
+      return per_stage(i, blocks) * (chain && blocks > NUM_CU ? 1.2 : 1.0);
+    };
+    double best = 1e300;
+    if (shared) best = fixed + s2[2] * (double)s.iters / s.nblocks + 9.0 + 0.03 * s.nblocks;
+    Shape c = s;
+    for (int i = 2; i >= 0; --i) {
+      c.bn = 64 + 32 * i;
+      c.tiles_n0 = (int)ceil_div(b.p[0].N, c.bn);
+      c.tiles_n = c.tiles_n0 + (b.nprob > 1 ? (int)ceil_div(b.p[1].N, c.bn) : 0);
+      c.tiles = c.tiles_m * c.tiles_n;
+      c.iters = (int64_t)c.tiles * c.ktiles;
+      c.splits = 1;
+      c.nblocks = c.tiles;
+      c.chain = chain;
+      const int rem = c.tiles % slots;
+      const double t = (c.tiles / slots) * (fixed + whole_stage(i, slots) * c.ktiles) +
+                       (rem == 0 ? 0 : fixed + whole_stage(i, rem) * c.ktiles);
+      if (t < best && !(chain && c.bn == BN)) {  // (no registers for CHAIN at 128)
+        best = t;
+        s = c;
+      }
+      c.splits = std::min(c.ktiles, slots / c.tiles);  // 0 for more tiles than slots
+      if (parts > 1 && c.splits >= parts) {  // as many parts as above: as accurate
+        c.nblocks = c.tiles * c.splits;
+        c.chain = 0;
+        const double ts = fixed + per_stage(i, c.nblocks) * (double)ceil_div(c.ktiles, c.splits) +
+                          9.0 + 0.03 * c.nblocks * c.bn / BN;
+        if (ts < best) {
+          best = ts;
+          s = c;
+        }
+      }
+    }
+  }
   return s;
 }
 
 static bool batch_ok(const GemmBatch& b) {
   if (b.nprob < 1 || b.nprob > 2) return false;
-  const int BK = b.mode == GEMM_BF16 ? BK16 : b.mode == GEMM_SPLIT ? BKS : gnnprop::BK;
+  const int BK = stage_k(b);
   if (b.nprob == 2) {
     if (b.p[0].M != b.p[1].M) return false;
     const auto kt = [BK](const GemmProblem& p) {
@@ -1499,7 +1897,7 @@ size_t gemm_workspace_bytes(const GemmBatch& b) {
   const Shape s = gemm_shape(b);
   if (s.tiles == 0 || s.nblocks == s.tiles) return 0;
   const size_t slots = s.splits > 1 ? (size_t)s.nblocks : (size_t)s.nblocks * 2;
-  return round_up(slots * BM * BN * 4, 256);
+  return round_up(slots * BM * s.bn * 4, 256);
 }
 
 double gemm_flops(const GemmBatch& b) {
@@ -1514,7 +1912,7 @@ double gemm_flops(const GemmBatch& b) {
 // The reduction of a launch's shared tiles as its own kernel.
 static hipError_t fixup_launch(const GemmKArgs& g, hipStream_t s) {
   timer_begin(GNN_K_GEMM_REDUCE, s);
-  gemm_fixup_kernel<<<dim3((unsigned)g.tiles, FIX_CHUNKS), 256, 0, s>>>(g);
+  gemm_fixup_kernel<<<dim3((unsigned)g.tiles, (unsigned)fix_chunks(g.bn)), 256, 0, s>>>(g);
   timer_end(GNN_K_GEMM_REDUCE, 0.0, s);
   return hipGetLastError();
 }
@@ -1558,10 +1956,12 @@ hipError_t gemm_launch(const GemmBatch& b, void* workspace, size_t ws_bytes,
   g.iters = sh.iters;
   g.nblocks = sh.nblocks;
   g.splits = sh.splits;
+  g.bn = sh.bn;
   bool va = true, vb = true;
   // 4 consecutive elements per load: 16 bytes (fp32) or 8 (bf16 storage)
   auto vec_ok = [](const void* p, int64_t ld, bool h) {
-    return h ? (reinterpret_cast<uintptr_t>(p) % 8 == 0 && ld % 4 == 0) : vec4_ok(p, ld);
+    return ld < (1 << 23) &&
+           (h ? (reinterpret_cast<uintptr_t>(p) % 8 == 0 && ld % 4 == 0) : vec4_ok(p, ld));
   };
   for (int i = 0; i < b.nprob; ++i) {
     g.p[i] = b.p[i];
@@ -1595,7 +1995,7 @@ hipError_t gemm_launch(const GemmBatch& b, void* workspace, size_t ws_bytes,
   int extra = 0;
   if (pending && pending->pending) {
     memcpy(&fx, pending->args, sizeof(fx));
-    extra = fx.tiles * FIX_CHUNKS;
+    extra = fx.tiles * fix_chunks(fx.bn);
   }
   const unsigned grid = (unsigned)(sh.nblocks + extra);
   const int kid = b.trans_a ? (b.trans_b ? GNN_K_GEMM_TT : GNN_K_GEMM_TN)
@@ -1623,28 +2023,34 @@ hipError_t gemm_launch(const GemmBatch& b, void* workspace, size_t ws_bytes,
       gemm_f32_kernel<false, true><<<grid, 256, 0, s>>>(g, fx);
     else
       gemm_f32_kernel<true, true><<<grid, 256, 0, s>>>(g, fx);
-  } else if (b.b_planes && !b.trans_a) {
-    if (!b.trans_b)
-      gemm_split_kernel<false, false, true, 8><<<grid, 512, 0, s>>>(g, fx);
-    else
-      gemm_split_kernel<false, true, true, 8><<<grid, 512, 0, s>>>(g, fx);
   } else if (b.b_planes) {
-    if (!b.trans_a && !b.trans_b)
-      gemm_split_kernel<false, false, true><<<grid, 256, 0, s>>>(g, fx);
-    else if (b.trans_a && !b.trans_b)
-      gemm_split_kernel<true, false, true><<<grid, 256, 0, s>>>(g, fx);
-    else if (!b.trans_a && b.trans_b)
-      gemm_split_kernel<false, true, true><<<grid, 256, 0, s>>>(g, fx);
+    auto width = [&](auto at, auto chain) {
+      constexpr bool AT = decltype(at)::value, CH = decltype(chain)::value;
+      if (sh.bn == 64)
+        gemm_planes_kernel<AT, 2, CH><<<grid, 256, 0, s>>>(g, fx);
+      else if (sh.bn == 96)
+        gemm_planes_kernel<AT, 3, CH><<<grid, 256, 0, s>>>(g, fx);
+      else if constexpr (!CH)
+        gemm_planes_kernel<AT, 4, false><<<grid, 256, 0, s>>>(g, fx);
+    };
+    auto trans = [&](auto chain) {
+      if (b.trans_a)
+        width(std::true_type{}, chain);
+      else
+        width(std::false_type{}, chain);
+    };
+    if (sh.chain)
+      trans(std::true_type{});
     else
-      gemm_split_kernel<true, true, true><<<grid, 256, 0, s>>>(g, fx);
+      trans(std::false_type{});
   } else if (!b.trans_a && !b.trans_b) {
-    gemm_split_kernel<false, false, false, 8><<<grid, 512, 0, s>>>(g, fx);
+    gemm_split_kernel<false, false, 8><<<grid, 512, 0, s>>>(g, fx);
   } else if (b.trans_a && !b.trans_b) {
-    gemm_split_kernel<true, false, false><<<grid, 256, 0, s>>>(g, fx);
+    gemm_split_kernel<true, false><<<grid, 256, 0, s>>>(g, fx);
   } else if (!b.trans_a && b.trans_b) {
-    gemm_split_kernel<false, true, false, 8><<<grid, 512, 0, s>>>(g, fx);
+    gemm_split_kernel<false, true, 8><<<grid, 512, 0, s>>>(g, fx);
   } else {
-    gemm_split_kernel<true, true, false><<<grid, 256, 0, s>>>(g, fx);
+    gemm_split_kernel<true, true><<<grid, 256, 0, s>>>(g, fx);
   }
   timer_end(kid, gemm_flops(b), s);
   hipError_t e = hipGetLastError();

@@ -191,6 +191,18 @@ struct SplitJob {
 constexpr int MAX_SPLIT_JOBS = 4;
 // Up to MAX_SPLIT_JOBS matrices split in one launch.
 hipError_t split_b_planes_launch(const SplitJob* jobs, int njobs, hipStream_t s);
+// Whether a product of M rows takes its B operand as planes: split products
+// of at least four row tiles of 128, each of which would otherwise split the
+// same values again.
+bool gemm_use_planes(int32_t M, int32_t mode);
+// The batch with b_planes set by that rule (its workspace size and launch
+// depend on it).
+GemmBatch gemm_with_planes(GemmBatch b);
+// Bytes of the planes of every B operand of n batches marked b_planes, and
+// their splitting (one launch per MAX_SPLIT_JOBS operands), which points the
+// batches at them.
+size_t gemm_planes_bytes(const GemmBatch* b, int n);
+hipError_t gemm_split_planes(GemmBatch* b, int n, void* planes, hipStream_t s);
 size_t gemm_workspace_bytes(const GemmBatch& b);
 // The reduction of a stream-K or split-K launch's shared tiles, held back so
 // that the next GEMM launch on the stream runs it in extra blocks of its own

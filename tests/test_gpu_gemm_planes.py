@@ -1,0 +1,58 @@
+"""Split products whose B comes as ready pieces (M >= 512): every tile width,
+whole and split tiles, partial stages and edges, against the double-precision
+product.
+
+Bound, per element: an output adds up 6 ceil(K / 32) piece products, each in at
+most two steps that lose up to 2^-23 of a partial sum, which is at most
+(|A| |B|)[i, j]; the pieces left out are below 2^-24 of each product, and a
+reduction over parts adds a rounding per part (fewer than 8 + the steps)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2010_03166_amd import gnnprop as G
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    (512, 1, 1), (512, 16, 31), (513, 64, 32), (640, 63, 33),      # narrow, partial stages
+    (600, 65, 40), (1000, 96, 96), (1023, 97, 127), (700, 129, 64),
+    (1000, 256, 256),   # few tiles: whole, chained sums
+    (2000, 200, 500),   # whole, 64 columns, chained
+    (4000, 41, 1000),   # split along K, 64 columns
+    (8000, 96, 41),     # two stages, the last one partial
+    (8000, 602, 70),    # 96 columns
+    (8003, 512, 200),   # two blocks per CU, moved-back rows
+    (20000, 600, 65),   # more tiles than slots
+]
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("pad", [0, 1])
+def test_split_planes(M, N, K, ta, tb, pad):
+    gen = torch.Generator().manual_seed(M + 3 * N + 7 * K)
+    a = torch.randn((M, K), generator=gen)
+    b = torch.randn((K, N), generator=gen)
+
+    def stored(x, trans):
+        x = x.T if trans else x
+        # padded to float4 rows, or off them
+        ld = -(-x.shape[1] // 4) * 4 + pad
+        buf = torch.full((x.shape[0], ld), float("nan"))
+        buf[:, : x.shape[1]] = x
+        return buf.cuda()
+
+    A, B = stored(a, ta), stored(b, tb)
+    ldc = -(-N // 4) * 4 + pad
+    C = torch.full((M, ldc), float("nan"), device="cuda")
+    ws = torch.empty(max(G.gnn_gemm_workspace_bytes(M, N, K), 256), dtype=torch.uint8,
+                     device="cuda")
+    G.gnn_gemm(ta, tb, M, N, K, A, A.stride(0), B, B.stride(0), C, ldc, 0, ws)
+    torch.cuda.synchronize()
+    got = C.cpu().numpy().astype(np.float64)
+    assert np.isnan(got[:, N:]).all()  # nothing past the row's end
+    ad, bd = a.numpy().astype(np.float64), b.numpy().astype(np.float64)
+    err = np.abs(got[:, :N] - ad @ bd)
+    bound = (12 * -(-K // 32) + 8) * 2.0 ** -23 * (np.abs(ad) @ np.abs(bd))
+    assert (err <= bound).all(), float((err / bound).max())
