@@ -158,13 +158,13 @@ gnn_status check_gat(const gnn_csr* csr, const gnn_layer* L, float alpha) {
 
 // saved: P (n x ld_h), s, t (n), att (nnz).
 // workspace: G (n x ld_h), dP (n x ld_h), dz, dz_t, att_t (nnz), [ds; dt]
-// (2 x ld_n), column-sum partials, GEMM partials.
+// (2 x ld_n), column-sum partials, the weight's planes, GEMM partials.
 struct GatLayout {
   int64_t ld_h, ld_n;
   size_t s_p, s_s, s_t, s_att, saved;
   // GEMM workspace: [w_gemm, w_gemm_x) the weight gradient's partial tiles,
   // summed by the input-gradient launch; [w_gemm_x, total) the rest
-  size_t w_g, w_dp, w_dz, w_dzt, w_att_t, w_dsdt, w_cs, w_gemm, w_gemm_x, total;
+  size_t w_g, w_dp, w_dz, w_dzt, w_att_t, w_dsdt, w_cs, w_wp, w_gemm, w_gemm_x, total;
 };
 
 GatLayout gat_layout(const gnn_csr* csr, const gnn_layer* L) {
@@ -183,9 +183,9 @@ GatLayout gat_layout(const gnn_csr* csr, const gnn_layer* L) {
   o.saved = o.s_att + eb;
   const size_t gw =
       gemm_workspace_bytes(gemm1(1, 0, f_in, h, n, 0, f_in, 0, h, 0, h, 0, L->flags));
-  const size_t g = std::max(
-      gemm_workspace_bytes(gemm1(0, 0, n, h, f_in, 0, f_in, 0, h, 0, h, 0, L->flags)),
-      gemm_workspace_bytes(gemm1(0, 1, n, f_in, h, 0, h, 0, h, 0, f_in, 0, L->flags)));
+  const GemmBatch fwd = gemm_with_planes(gemm1(0, 0, n, h, f_in, 0, f_in, 0, h, 0, h, 0, L->flags));
+  const GemmBatch bwd = gemm_with_planes(gemm1(0, 1, n, f_in, h, 0, h, 0, h, 0, f_in, 0, L->flags));
+  const size_t g = std::max(gemm_workspace_bytes(fwd), gemm_workspace_bytes(bwd));
   o.w_g = 0;
   o.w_dp = nh;
   o.w_dz = o.w_dp + nh;
@@ -193,7 +193,8 @@ GatLayout gat_layout(const gnn_csr* csr, const gnn_layer* L) {
   o.w_att_t = o.w_dzt + eb;
   o.w_dsdt = o.w_att_t + eb;
   o.w_cs = o.w_dsdt + round_up((size_t)2 * o.ld_n * 4, 256);
-  o.w_gemm = o.w_cs + colsum_partials_bytes(n, h, 2);
+  o.w_wp = o.w_cs + colsum_partials_bytes(n, h, 2);
+  o.w_gemm = o.w_wp + std::max(gemm_planes_bytes(&fwd, 1), gemm_planes_bytes(&bwd, 1));
   o.w_gemm_x = o.w_gemm + round_up(gw, 256);
   o.total = o.w_gemm_x + round_up(g, 256);
   return o;
@@ -253,9 +254,10 @@ gnn_status gnn_gat_fwd(const gnn_csr* csr, const gnn_layer* layer, const float* 
   float* t = reinterpret_cast<float*>(sv + o.s_t);
   float* att = reinterpret_cast<float*>(sv + o.s_att);
   char* ws = static_cast<char*>(workspace);
-  GNN_HIP(gemm_launch(gemm1(0, 0, n, h, f_in, X, layer->ld_x, W, h, P, o.ld_h, 0,
-                            layer->flags),
-                      ws + o.w_gemm, o.total - o.w_gemm, stream));
+  GemmBatch g = gemm_with_planes(gemm1(0, 0, n, h, f_in, X, layer->ld_x, W, h, P, o.ld_h, 0,
+                                       layer->flags));
+  GNN_HIP(gemm_split_planes(&g, 1, ws + o.w_wp, stream));
+  GNN_HIP(gemm_launch(g, ws + o.w_gemm, o.total - o.w_gemm, stream));
   gat_scores_kernel<<<(unsigned)ceil_div(n, 4), 256, 0, stream>>>(n, h, P, o.ld_h, a, s, t);
   if (nnz > 0)
     gat_att_kernel<<<(unsigned)ceil_div(nnz, 256), 256, 0, stream>>>(
@@ -360,10 +362,12 @@ gnn_status gnn_gat_bwd(const gnn_csr* csr, const gnn_layer* layer, const float* 
   GNN_HIP(gemm_launch(gemm1(1, 0, f_in, h, n, X, layer->ld_x, dP, o.ld_h, dW, h, 0,
                             layer->flags), ws + o.w_gemm, o.w_gemm_x - o.w_gemm, stream,
                       dX ? &held : nullptr));
-  if (dX)
-    GNN_HIP(gemm_launch(gemm1(0, 1, n, f_in, h, dP, o.ld_h, W, h, dX, layer->ld_dx, 0,
-                              layer->flags), ws + o.w_gemm_x, o.total - o.w_gemm_x, stream,
-                        nullptr, &held));
+  if (dX) {
+    GemmBatch g = gemm_with_planes(gemm1(0, 1, n, f_in, h, dP, o.ld_h, W, h, dX, layer->ld_dx, 0,
+                                         layer->flags));
+    GNN_HIP(gemm_split_planes(&g, 1, ws + o.w_wp, stream));
+    GNN_HIP(gemm_launch(g, ws + o.w_gemm_x, o.total - o.w_gemm_x, stream, nullptr, &held));
+  }
   return GNN_OK;
 }
 

@@ -183,8 +183,9 @@ struct ClsLayout {
   int64_t ld_c;
   int nblk;
   // GEMM workspace: [off_gemm, off_gemm_x) the weight gradient's partial
-  // tiles, summed by the input-gradient launch; [off_gemm_x, total) the rest
-  size_t off_m, off_g, off_part, off_gemm, off_gemm_x, total;
+  // tiles, summed by the input-gradient launch; [off_gemm_x, off_wp) the rest
+  // and then W's planes for both of its products
+  size_t off_m, off_g, off_part, off_gemm, off_gemm_x, off_wp, total;
 };
 
 GemmBatch prod(int ta, int tb, int32_t M, int32_t N, int32_t K, const float* A,
@@ -211,15 +212,17 @@ ClsLayout cls_layout(int32_t n, int32_t f, int32_t C, uint32_t flags) {
   o.ld_c = round_up(C, 4);
   o.nblk = (int)std::max<int64_t>(1, ceil_div(n, LOSS_ROWS));
   const size_t gw = gemm_workspace_bytes(prod(1, 0, f, C, n, 0, f, 0, C, 0, C, 0, flags));
+  const GemmBatch weight[2] = {gemm_with_planes(prod(0, 0, n, C, f, 0, f, 0, C, 0, C, 1, flags)),
+                               gemm_with_planes(prod(0, 1, n, f, C, 0, C, 0, C, 0, f, 0, flags))};
   const size_t g =
-      std::max(gemm_workspace_bytes(prod(0, 0, n, C, f, 0, f, 0, C, 0, C, 1, flags)),
-               gemm_workspace_bytes(prod(0, 1, n, f, C, 0, C, 0, C, 0, f, 0, flags)));
+      std::max(gemm_workspace_bytes(weight[0]), gemm_workspace_bytes(weight[1]));
   o.off_m = 0;
   o.off_g = round_up((size_t)n * o.ld_c * 4, 256);
   o.off_part = o.off_g + round_up((size_t)n * o.ld_c * 4, 256);
   o.off_gemm = o.off_part + round_up((size_t)o.nblk * 4, 256);
   o.off_gemm_x = o.off_gemm + round_up(gw, 256);
-  o.total = o.off_gemm_x + round_up(g, 256);
+  o.off_wp = o.off_gemm_x + round_up(g, 256);
+  o.total = o.off_wp + gemm_planes_bytes(weight, 2);
   return o;
 }
 
@@ -274,10 +277,14 @@ gnn_status gnn_classifier(int32_t n, int32_t f, int32_t C, int32_t kind,
   float* G = reinterpret_cast<float*>(ws + o.off_g);
   float* part = reinterpret_cast<float*>(ws + o.off_part);
   void* gws = ws + o.off_gemm;
-  const size_t gws_bytes = o.total - o.off_gemm;
+  const size_t gws_bytes = o.off_wp - o.off_gemm;
+  // the two products with W, its pieces for both split in one launch
+  GemmBatch weight[2] = {
+      gemm_with_planes(prod(0, 0, n, C, f, X, ld_x, W, C, XM, ld_m, 1, flags)),
+      gemm_with_planes(prod(0, 1, n, f, C, G, o.ld_c, W, C, dX, ld_dx, 0, flags))};
   if (n > 0) {
-    GNN_HIP(gemm_launch(prod(0, 0, n, C, f, X, ld_x, W, C, XM, ld_m, 1, flags), gws,
-                        gws_bytes, stream));
+    GNN_HIP(gemm_split_planes(weight, dX ? 2 : 1, ws + o.off_wp, stream));
+    GNN_HIP(gemm_launch(weight[0], gws, gws_bytes, stream));
     timer_begin(GNN_K_LOSS, stream);
     if (kind == GNN_LOSS_SOFTMAX)
       loss_grad_kernel<GNN_LOSS_SOFTMAX><<<o.nblk, 64 * LOSS_ROWS, 0, stream>>>(
@@ -302,8 +309,8 @@ gnn_status gnn_classifier(int32_t n, int32_t f, int32_t C, int32_t kind,
   GNN_HIP(gemm_launch(prod(1, 0, f, C, n, X, ld_x, G, o.ld_c, dW, C, 0, flags), gws,
                       o.off_gemm_x - o.off_gemm, stream, dX ? &held : nullptr));
   if (dX)
-    GNN_HIP(gemm_launch(prod(0, 1, n, f, C, G, o.ld_c, W, C, dX, ld_dx, 0, flags),
-                        ws + o.off_gemm_x, o.total - o.off_gemm_x, stream, nullptr, &held));
+    GNN_HIP(gemm_launch(weight[1], ws + o.off_gemm_x, o.off_wp - o.off_gemm_x, stream, nullptr,
+                        &held));
   return GNN_OK;
 }
 

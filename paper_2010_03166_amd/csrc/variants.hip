@@ -47,6 +47,13 @@ GemmBatch gemm1(int trans_a, int trans_b, int32_t M, int32_t N, int32_t K,
   return b;
 }
 
+// A product with a weight as B, by planes where the rule says so.
+GemmBatch gemm1w(int trans_b, int32_t M, int32_t N, int32_t K, const float* A, int64_t lda,
+                 const float* W, int64_t ldw, float* C, int64_t ldc, const float* bias, int relu,
+                 uint32_t flags) {
+  return gemm_with_planes(gemm1(0, trans_b, M, N, K, A, lda, W, ldw, C, ldc, bias, relu, flags));
+}
+
 // Two products of the same M and K in one launch.
 GemmBatch gemm2(const GemmBatch& a, const GemmBatch& b) {
   GemmBatch c = a;
@@ -73,7 +80,7 @@ struct GcnLayout {
   int64_t ld_s, ld_h, ld_b;
   // GEMM workspace: [off_gemm, off_gemm_x) the weight gradient's partial
   // tiles, summed by the input-gradient launch; [off_gemm_x, off_cs) the rest
-  size_t off_a, off_b, off_gemm, off_gemm_x, off_cs, total;
+  size_t off_a, off_b, off_gemm, off_gemm_x, off_cs, off_wp, total;
 };
 
 GcnLayout gcn_layout(const gnn_csr* csr, const gnn_layer* L) {
@@ -86,15 +93,16 @@ GcnLayout gcn_layout(const gnn_csr* csr, const gnn_layer* L) {
   const size_t a = (size_t)n * o.ld_h * 4;  // P or G
   const size_t b = (size_t)n * o.ld_b * 4;  // T or V
   const size_t gw = gemm_ws(gemm1(1, 0, f_in, h, n, 0, f_in, 0, h, 0, h, 0, 0, L->flags));
-  const size_t g =
-      std::max(gemm_ws(gemm1(0, 0, n, h, f_in, 0, f_in, 0, h, 0, h, 0, 0, L->flags)),
-               gemm_ws(gemm1(0, 1, n, f_in, h, 0, h, 0, h, 0, f_in, 0, 0, L->flags)));
+  const GemmBatch fwd = gemm1w(0, n, h, f_in, 0, f_in, 0, h, 0, h, 0, 0, L->flags);
+  const GemmBatch bwd = gemm1w(1, n, f_in, h, 0, h, 0, h, 0, f_in, 0, 0, L->flags);
+  const size_t g = std::max(gemm_ws(fwd), gemm_ws(bwd));
   o.off_a = 0;
   o.off_b = round_up(a, 256);
   o.off_gemm = o.off_b + round_up(b, 256);
   o.off_gemm_x = o.off_gemm + round_up(gw, 256);
   o.off_cs = o.off_gemm_x + round_up(g, 256);
-  o.total = o.off_cs + colsum_partials_bytes(n, h);
+  o.off_wp = o.off_cs + colsum_partials_bytes(n, h);
+  o.total = o.off_wp + std::max(gemm_planes_bytes(&fwd, 1), gemm_planes_bytes(&bwd, 1));
   return o;
 }
 
@@ -106,7 +114,8 @@ struct MixLayout {
   // between [off_gemm, off_gemm + gw) and the gw bytes after it (each
   // launch sums its predecessor's, the first input-gradient launch the
   // last's); [off_gemm_x, off_cs) serves the other launches
-  size_t saved, off_g, off_r0, off_r1, off_gemm, gw, off_gemm_x, off_cs, total;
+  // off_wp: the planes of every hop's weight, wp bytes each
+  size_t saved, off_g, off_r0, off_r1, off_gemm, gw, off_gemm_x, off_cs, off_wp, wp, total;
 };
 
 MixLayout mix_layout(const gnn_csr* csr, const gnn_layer* L, int32_t K) {
@@ -118,7 +127,8 @@ MixLayout mix_layout(const gnn_csr* csr, const gnn_layer* L, int32_t K) {
   o.ld_r = round_up(f_in, 4);
   o.saved = (size_t)K * n * o.ld_s * 4;
   size_t g = 0, gw = 0;
-  const GemmBatch f = gemm1(0, 0, n, h, f_in, 0, f_in, 0, wy, 0, wy, 0, 1, L->flags);
+  const GemmBatch f = gemm1w(0, n, h, f_in, 0, f_in, 0, wy, 0, wy, 0, 1, L->flags);
+  const GemmBatch x = gemm1w(1, n, f_in, h, 0, wy, 0, wy, 0, f_in, 0, 0, L->flags);
   const GemmBatch w = gemm1(1, 0, f_in, h, n, 0, f_in, 0, wy, 0, wy, 0, 0, L->flags);
   // hops go two per launch, the last one alone when K + 1 is odd; the work
   // split (and so the workspace) differs between the two shapes
@@ -128,7 +138,7 @@ MixLayout mix_layout(const gnn_csr* csr, const gnn_layer* L, int32_t K) {
     g = std::max(g, gemm_ws(gemm2(f, f)));
     gw = std::max(gw, gemm_ws(gemm2(w, w)));
   }
-  g = std::max(g, gemm_ws(gemm1(0, 1, n, f_in, h, 0, wy, 0, wy, 0, f_in, 0, 0, L->flags)));
+  g = std::max(g, gemm_ws(x));
   o.gw = round_up(gw, 256);
   o.off_g = 0;
   o.off_r0 = round_up((size_t)n * o.ld_g * 4, 256);
@@ -136,7 +146,9 @@ MixLayout mix_layout(const gnn_csr* csr, const gnn_layer* L, int32_t K) {
   o.off_gemm = o.off_r1 + round_up((size_t)n * o.ld_r * 4, 256);
   o.off_gemm_x = o.off_gemm + (K >= 2 ? 2 : 1) * o.gw;  // K >= 2: several dW launches
   o.off_cs = o.off_gemm_x + round_up(g, 256);
-  o.total = o.off_cs + colsum_partials_bytes(n, wy);
+  o.off_wp = o.off_cs + colsum_partials_bytes(n, wy);
+  o.wp = std::max(gemm_planes_bytes(&f, 1), gemm_planes_bytes(&x, 1));
+  o.total = o.off_wp + (K + 1) * o.wp;
   return o;
 }
 
@@ -181,12 +193,15 @@ gnn_status gnn_gcn_fwd(const gnn_csr* csr, const gnn_layer* layer,
   if (o.order == 1) {
     float* S = static_cast<float*>(saved);
     GNN_HIP(spmm_launch(spmm_call(csr, false, f_in, X, layer->ld_x, S, o.ld_s), stream));
-    GNN_HIP(gemm_launch(gemm1(0, 0, n, h, f_in, S, o.ld_s, W, h, Y, layer->ld_y, b, 1,
-                              layer->flags), gws, gws_bytes, stream));
+    GemmBatch g = gemm1w(0, n, h, f_in, S, o.ld_s, W, h, Y, layer->ld_y, b, 1, layer->flags);
+    GNN_HIP(gemm_split_planes(&g, 1, ws + o.off_wp, stream));
+    GNN_HIP(gemm_launch(g, gws, gws_bytes, stream));
   } else {
     float* P = reinterpret_cast<float*>(ws + o.off_a);
-    GNN_HIP(gemm_launch(gemm1(0, 0, n, h, f_in, X, layer->ld_x, W, h, P, o.ld_h, nullptr,
-                              0, layer->flags), gws, gws_bytes, stream));
+    GemmBatch g = gemm1w(0, n, h, f_in, X, layer->ld_x, W, h, P, o.ld_h, nullptr, 0,
+                         layer->flags);
+    GNN_HIP(gemm_split_planes(&g, 1, ws + o.off_wp, stream));
+    GNN_HIP(gemm_launch(g, gws, gws_bytes, stream));
     SpmmCall c = spmm_call(csr, false, h, P, o.ld_h, Y, layer->ld_y);
     c.epilogue = SPMM_BIAS_RELU;
     c.bias = b;
@@ -241,8 +256,9 @@ gnn_status gnn_gcn_bwd(const gnn_csr* csr, const gnn_layer* layer,
                               layer->flags), wws, wws_bytes, stream, dX ? &held : nullptr));
     if (dX) {
       float* V = B;
-      GNN_HIP(gemm_launch(gemm1(0, 1, n, f_in, h, G, o.ld_h, W, h, V, o.ld_b, nullptr, 0,
-                                layer->flags), xws, xws_bytes, stream, nullptr, &held));
+      GemmBatch g = gemm1w(1, n, f_in, h, G, o.ld_h, W, h, V, o.ld_b, nullptr, 0, layer->flags);
+      GNN_HIP(gemm_split_planes(&g, 1, ws + o.off_wp, stream));
+      GNN_HIP(gemm_launch(g, xws, xws_bytes, stream, nullptr, &held));
       GNN_HIP(spmm_launch(spmm_call(csr, true, f_in, V, o.ld_b, dX, layer->ld_dx), stream));
     }
   } else {
@@ -250,10 +266,12 @@ gnn_status gnn_gcn_bwd(const gnn_csr* csr, const gnn_layer* layer,
     GNN_HIP(spmm_launch(spmm_call(csr, true, h, G, o.ld_h, T, o.ld_b), stream));
     GNN_HIP(gemm_launch(gemm1(1, 0, f_in, h, n, X, layer->ld_x, T, o.ld_b, dW, h, nullptr,
                               0, layer->flags), wws, wws_bytes, stream, dX ? &held : nullptr));
-    if (dX)
-      GNN_HIP(gemm_launch(gemm1(0, 1, n, f_in, h, T, o.ld_b, W, h, dX, layer->ld_dx,
-                                nullptr, 0, layer->flags), xws, xws_bytes, stream, nullptr,
-                          &held));
+    if (dX) {
+      GemmBatch g = gemm1w(1, n, f_in, h, T, o.ld_b, W, h, dX, layer->ld_dx, nullptr, 0,
+                           layer->flags);
+      GNN_HIP(gemm_split_planes(&g, 1, ws + o.off_wp, stream));
+      GNN_HIP(gemm_launch(g, xws, xws_bytes, stream, nullptr, &held));
+    }
   }
   if (db) GNN_HIP(colsum_launch(n, h, G, o.ld_h, db, cspart, stream));
   return GNN_OK;
@@ -308,13 +326,18 @@ gnn_status gnn_mixhop_fwd(const gnn_csr* csr, const gnn_layer* layer,
     GNN_HIP(spmm_launch(spmm_call(csr, false, f_in, S(k - 1), ldS(k - 1),
                                   Sv + (size_t)(k - 1) * n * o.ld_s, o.ld_s), stream));
   auto hop = [&](int k) {
-    return gemm1(0, 0, n, h, f_in, S(k), ldS(k), W + (size_t)k * h, wy,
-                 Y + (size_t)k * h, layer->ld_y, b ? b + (size_t)k * h : nullptr, 1,
-                 layer->flags);
+    return gemm1w(0, n, h, f_in, S(k), ldS(k), W + (size_t)k * h, wy,
+                  Y + (size_t)k * h, layer->ld_y, b ? b + (size_t)k * h : nullptr, 1,
+                  layer->flags);
   };
-  for (int k = 0; k <= K; k += 2) {
-    const GemmBatch bt = k + 1 <= K ? gemm2(hop(k), hop(k + 1)) : hop(k);
-    GNN_HIP(gemm_launch(bt, gws, gws_bytes, stream));
+  // two hops per launch, their weights split in one launch per four hops
+  for (int k0 = 0; k0 <= K; k0 += 4) {
+    GemmBatch bt[2];
+    int nb = 0;
+    for (int k = k0; k <= K && k < k0 + 4; k += 2)
+      bt[nb++] = k + 1 <= K ? gemm2(hop(k), hop(k + 1)) : hop(k);
+    GNN_HIP(gemm_split_planes(bt, nb, ws + o.off_wp + k0 * o.wp, stream));
+    for (int i = 0; i < nb; ++i) GNN_HIP(gemm_launch(bt[i], gws, gws_bytes, stream));
   }
   return GNN_OK;
 }
@@ -383,17 +406,33 @@ gnn_status gnn_mixhop_bwd(const gnn_csr* csr, const gnn_layer* layer,
     // Horner: R = G_K W_K^T;  R = G_k W_k^T + A_hat^T R for k = K-1 .. 0,
     // the last step written into dX.
     auto vk = [&](int k, float* out, int64_t ld_out) {
-      return gemm1(0, 1, n, f_in, h, G + (size_t)k * h, o.ld_g, W + (size_t)k * h, wy,
-                   out, ld_out, nullptr, 0, layer->flags);
+      return gemm1w(1, n, f_in, h, G + (size_t)k * h, o.ld_g, W + (size_t)k * h, wy,
+                    out, ld_out, nullptr, 0, layer->flags);
+    };
+    // the products from hop K down; the weights of the next four hops are
+    // split in one launch whenever those of the last four are used up
+    GemmBatch bt[4];
+    auto product = [&](int k, float* out, int64_t ld_out, const GemmFixup* pending) -> hipError_t {
+      const int i = (K - k) % 4;
+      if (i == 0) {
+        int nb = 0;
+        for (int q = k; q >= 0 && nb < 4; --q) bt[nb++] = vk(q, nullptr, f_in);
+        const hipError_t e =
+            gemm_split_planes(bt, nb, ws + o.off_wp + (size_t)(K - k) * o.wp, stream);
+        if (e != hipSuccess) return e;
+      }
+      bt[i].p[0].C = out;
+      bt[i].p[0].ldc = ld_out;
+      return gemm_launch(bt[i], xws, xws_bytes, stream, nullptr, pending);
     };
     int cur = 0;
     float* r = K == 0 ? dX : R[cur];
     int64_t ld_r = K == 0 ? layer->ld_dx : o.ld_r;
-    GNN_HIP(gemm_launch(vk(K, r, ld_r), xws, xws_bytes, stream, nullptr, pend));
+    GNN_HIP(product(K, r, ld_r, pend));
     for (int k = K - 1; k >= 0; --k) {
       float* nx = k == 0 ? dX : R[cur ^ 1];
       const int64_t ld_nx = k == 0 ? layer->ld_dx : o.ld_r;
-      GNN_HIP(gemm_launch(vk(k, nx, ld_nx), xws, xws_bytes, stream));
+      GNN_HIP(product(k, nx, ld_nx, nullptr));
       SpmmCall c = spmm_call(csr, true, f_in, r, ld_r, nx, ld_nx);
       c.epilogue = SPMM_ADD;
       c.res = nx;
