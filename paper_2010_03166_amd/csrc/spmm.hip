@@ -16,8 +16,8 @@
 // span all of them) is finished through LDS by the group holding its first
 // entry, adding the other groups' parts in group order.  One kernel, no
 // atomics, bit-reproducible, and work is balanced by entries, not rows.
-// Outputs of 32 columns and more are cut into 8 (or 16) column slices, each
-// XCD gathering from its own (the GPU form of the feature partition of
+// Outputs are cut into up to 8 column slices, each
+// XCD gathering from one of them (the GPU form of the feature partition of
 // Section 5.3, Theorem 2 / Algorithm 7, with each XCD's L2 as the cache a
 // slice should fit).
 #include "internal.hpp"
@@ -352,6 +352,7 @@ struct SpmmArgs {
   int32_t w;
   const float* in;
   int64_t ld_in;
+  uint32_t in_bytes;  // extent of `in` (below 4 GiB: OFF32)
   float* out;
   int64_t ld_out;
   int32_t epilogue;
@@ -360,7 +361,7 @@ struct SpmmArgs {
   int64_t ld_res;
   const float* mask;
   int64_t ld_mask;
-  int32_t nslices;  // column slices: 1, or a multiple of 8
+  int32_t nslices;  // column slices: 1, 2, 4 or 8
   int32_t sw;       // slice width in columns
   int32_t nwin;     // workgroups per slice: plan windows / wpb, rounded up
   int32_t wpb;      // consecutive plan windows per workgroup (1 or 2)
@@ -369,10 +370,10 @@ struct SpmmArgs {
 };
 
 // Column slices.  Blocks are dispatched round-robin over the 8 XCDs, so with
-// S = 8 P slices, block b = p (8 nwin) + 8 win + x works on slice 8 p + x of
-// window (group) win: XCD x gathers only from slices x, x + 8, ..., one pass after
-// the other, and each n x sw slice is sized to stay in that XCD's L2 (the
-// cache-sized feature partitions of Theorem 2 / Algorithm 7).
+// S slices (a power of two up to 8) block b works on slice b mod S of window
+// (group) b / S: an XCD gathers from one n x sw slice only, which its L2
+// holds or half holds (the cache-sized feature partitions of Theorem 2 /
+// Algorithm 7).  See spmm_args for S.
 //
 // A group of G lanes covers G * W consecutive columns of the slice per pass
 // (W = 4: float4 per lane, so one gathered 256-byte row segment of a
@@ -424,6 +425,16 @@ struct Vec<true> {
     v.w = fmaxf(v.w, 0.f);
     return v;
   }
+  // 16 bytes at in + off, zeros from byte `bytes` on
+  __device__ static T load_within(const float* in, uint32_t bytes, uint32_t off) {
+#ifdef __HIP_DEVICE_COMPILE__
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(in), 0, (int)bytes, 0x00020000);
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+#else
+    return T{};
+#endif
+  }
   // the first k (1..3) components only: the ragged end of a row whose width
   // is not a multiple of 4
   __device__ static T load_part(const float* p, int k) {
@@ -469,6 +480,9 @@ struct Vec<false> {
   __device__ static void scale(T& acc, float s) { acc *= s; }
   __device__ static T relu(T v) { return fmaxf(v, 0.f); }
   __device__ static T select_pos(T m, T v) { return m > 0.f ? v : 0.f; }
+  __device__ static T load_within(const float* in, uint32_t, uint32_t off) {
+    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(in) + off);
+  }
   __device__ static T load_part(const float* p, int) { return *p; }
   __device__ static void store_part(float* p, T v, int) { *p = v; }
   __device__ static void store_h(uint16_t* p, T v) { *p = (uint16_t)(pack_bf16(v, 0.f) & 0xffffu); }
@@ -492,13 +506,8 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs a) {
   __shared__ int head_row[256], tail_row[256], starts[256];
   auto gtid = [&](int g) { return (g / gpw) * 64 + (g % gpw) * G; };
 
-  int slice = 0, win = blockIdx.x;
-  if (a.nslices >= 8) {
-    const int per = 8 * a.nwin;
-    const int r = (int)(blockIdx.x % per);
-    slice = 8 * (int)(blockIdx.x / per) + (r & 7);
-    win = r >> 3;
-  }
+  const int slice = blockIdx.x & (a.nslices - 1);
+  const int win = blockIdx.x / a.nslices;
   // Consecutive windows own consecutive rows and entries (an empty window
   // inside a hub row starts and ends where the next row starts), so
   // windows k .. k + wpb - 1 together are one run of whole rows.
@@ -614,10 +623,17 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs a) {
           for (int u = 0; u < D; ++u) {
             const int idx = __shfl(fi, base + k + u);
             if (k + u < cnt && ok) {
-              if (OFF32)
-                x[u] = ld(reinterpret_cast<const float*>(
-                    reinterpret_cast<const char*>(in) +
-                    (((uint32_t)idx * ld_in + (uint32_t)col) << 2)));
+              // A ragged end is gathered as a whole float4 too (rows start on
+              // 16 bytes, so it ends inside the row's stride; past the end of
+              // the last row it reads zeros) and its unused components are
+              // not stored: a branch per gather would keep the D gathers from
+              // going out together (8,000 x 250: 24.2 -> 18.9 us).
+              const uint32_t off = ((uint32_t)idx * ld_in + (uint32_t)col) << 2;
+              if (OFF32 && RAG)
+                x[u] = V::load_within(in, a.in_bytes, off);
+              else if (OFF32)
+                x[u] = V::load(reinterpret_cast<const float*>(
+                    reinterpret_cast<const char*>(in) + off));
               else
                 x[u] = ld(in + (int64_t)idx * a.ld_in + col);
             } else {
@@ -705,13 +721,8 @@ __global__ __launch_bounds__(256) void spmm_floor_kernel(SpmmArgs a) {
   __shared__ T part[256];
   auto gtid = [&](int g) { return (g / gpw) * 64 + (g % gpw) * G; };
 
-  int slice = 0, win = blockIdx.x;
-  if (a.nslices >= 8) {
-    const int per = 8 * a.nwin;
-    const int r = (int)(blockIdx.x % per);
-    slice = 8 * (int)(blockIdx.x / per) + (r & 7);
-    win = r >> 3;
-  }
+  const int slice = blockIdx.x & (a.nslices - 1);
+  const int win = blockIdx.x / a.nslices;
   const int k0 = win * a.wpb, k1 = min(k0 + a.wpb, a.nblk) - 1;
   const int4 bi0 = a.binfo[k0], bi1 = a.binfo[k1];
   const int r_lo = bi0.x, r_hi = bi1.y, B = bi0.z, E = bi1.w;
@@ -759,10 +770,12 @@ __global__ __launch_bounds__(256) void spmm_floor_kernel(SpmmArgs a) {
         for (int u = 0; u < D; ++u) {
           const int idx = __shfl(fi, base + k + u);
           if (k + u < cnt && ok) {
-            if (OFF32)
-              x[u] = ld(reinterpret_cast<const float*>(
-                  reinterpret_cast<const char*>(in) +
-                  (((uint32_t)idx * ld_in + (uint32_t)col) << 2)));
+            const uint32_t off = ((uint32_t)idx * ld_in + (uint32_t)col) << 2;
+            if (OFF32 && RAG)
+              x[u] = V::load_within(in, a.in_bytes, off);
+            else if (OFF32)
+              x[u] = V::load(reinterpret_cast<const float*>(
+                  reinterpret_cast<const char*>(in) + off));
             else
               x[u] = ld(in + (int64_t)idx * a.ld_in + col);
           } else {
@@ -828,19 +841,19 @@ static void spmm_epi(const SpmmArgs& a, bool off32, hipStream_t s) {
 }
 
 // Lane group width for a slice row of `units` float4s (or floats): a power
-// of two covering it, or 10 lanes for the 10-unit rows of 8 slices (300
-// columns: six groups to a wavefront instead of four 16-lane groups with 6
-// idle lanes each, 8,000 x 300 aggregation 39.6 -> 35.8 us; with 16 slices,
-// 602 columns, 16 lanes stay faster: 44.4 against 45.8 us).  RAG: float4
+// of two covering it, or 12 or 20 lanes (48- and 80-column slices: five and
+// three groups to a wavefront, 4 idle lanes of 64, where 16 and 32 lanes
+// would leave 16 and 24 idle).  RAG: float4
 // lanes on a width that is not a multiple of 4 (the lane at the row's end
-// reads and writes its 1..3 columns one by one).
+// writes its 1..3 columns one by one).
 template <bool VEC, bool RAG>
 static void spmm_dispatch(const SpmmArgs& a, bool off32, hipStream_t s) {
   const int units = VEC ? ceil_div(a.sw, 4) : a.sw;  // column vectors per slice row
   if (units <= 4) return spmm_epi<4, VEC, RAG>(a, off32, s);
   if (units <= 8) return spmm_epi<8, VEC, RAG>(a, off32, s);
-  if (units == 10 && a.nslices == 8) return spmm_epi<10, VEC, RAG>(a, off32, s);
+  if (VEC && units <= 12) return spmm_epi<12, VEC, RAG>(a, off32, s);
   if (units <= 16) return spmm_epi<16, VEC, RAG>(a, off32, s);
+  if (VEC && units <= 20) return spmm_epi<20, VEC, RAG>(a, off32, s);
   if (units <= 32) return spmm_epi<32, VEC, RAG>(a, off32, s);
   return spmm_epi<64, VEC, RAG>(a, off32, s);
 }
@@ -868,6 +881,7 @@ static SpmmArgs spmm_args(const SpmmCall& c, bool* vec_out, bool* off32_out) {
   a.w = c.w;
   a.in = c.in;
   a.ld_in = c.ld_in;
+  a.in_bytes = (uint32_t)(((int64_t)(c.n - 1) * c.ld_in + c.w) * 4);
   a.out = c.out;
   a.ld_out = c.ld_out;
   a.epilogue = c.epilogue;
@@ -877,30 +891,6 @@ static SpmmArgs spmm_args(const SpmmCall& c, bool* vec_out, bool* off32_out) {
   a.mask = c.mask;
   a.ld_mask = c.ld_mask;
   a.weights = c.weights;
-  // 8 slices (one per XCD) from 32 columns up.  A lane group covers the
-  // float4 columns of a slice row (spmm_dispatch); when 8 slices need
-  // groups of more than 16 lanes with over a quarter of them idle (602
-  // columns: 76-column slices on 32 lanes), 16 slices are faster, having
-  // twice the groups, and so the gathers, in flight per block.
-  a.nslices = c.w >= 32 ? 8 : 1;
-  a.sw = (int32_t)round_up(ceil_div(c.w, a.nslices), 4);
-  if (a.nslices == 8 && a.sw > 64) {
-    const int units = a.sw / 4;
-    int g = 1;
-    while (g < units) g *= 2;
-    if (4 * units < 3 * g) {
-      a.nslices = 16;
-      a.sw = (int32_t)round_up(ceil_div(c.w, a.nslices), 4);
-    }
-  }
-  // Two windows per workgroup once the grid would pass 16,384 workgroups:
-  // each workgroup pays a chain of dependent loads (window record, entry
-  // metadata, first gathers) before its gathers stream, which a longer entry
-  // range amortises (50,000 nodes x 256 columns: 213 -> 175 us; 20,000 x
-  // 200: 80 -> 77 us); smaller launches keep one (8,000 x 512: even).
-  a.nblk = (int32_t)d.nblk;
-  a.wpb = d.nblk * a.nslices > 16384 ? 2 : 1;
-  a.nwin = (int32_t)ceil_div(d.nblk, (int64_t)a.wpb);
   // float4 lanes whenever rows start 16-byte aligned (the ragged end of a
   // width that is not a multiple of 4 is read and written per component)
   const bool out_ok = c.epilogue == SPMM_STORE_BF16
@@ -910,6 +900,39 @@ static SpmmArgs spmm_args(const SpmmCall& c, bool* vec_out, bool* off32_out) {
                    (c.epilogue != SPMM_BIAS_RELU || !c.bias || aligned16(c.bias)) &&
                    (c.epilogue != SPMM_ADD || vec4_ok(c.res, c.ld_res)) &&
                    (!c.mask || vec4_ok(c.mask, c.ld_mask));
+  // Column slices.  Each slice walks all entries (index, value, row: 12 bytes
+  // and their shuffles and row closings), so few, wide slices cost least per
+  // gathered byte; many, narrow ones keep the gathered rows in L2 and more
+  // workgroups in flight.  Measured best (us; 8 slices of a multiple of 4
+  // columns before): up to 64 columns one slice (50,000 x 64: 50, before
+  // 209), two up to 128 (20,000 x 128: 25, 65) and, from 1,500 windows on, to
+  // 256 (20,000 x 200: 39, 66; four slices 47) and four to 512 (50,000 x
+  // 300: 177, 258); smaller graphs take four up to 320 columns (8,000 x 300:
+  // 18.6, 23.8) and then eight, and twice as many while their workgroups
+  // would leave the chip short of them (8,000 x 128: 14.3 in two slices, 12.3
+  // in four).  Slices are a multiple of 16 columns wide, so that they start
+  // on 64 bytes wherever rows do and a gathered slice row touches no line
+  // more than it fills (8,000 x 602: eight of 80 columns 27.7 us, sixteen of
+  // 40 41.1).  Rows off 16-byte alignment (float lanes) keep eight slices.
+  if (vec) {
+    const bool many = d.nblk >= 1500;
+    a.nslices = c.w <= 64 ? 1
+                : c.w <= (many ? 256 : 128) ? 2
+                : c.w <= (many ? 512 : 320) ? 4 : 8;
+    while (a.nslices < 8 && d.nblk * a.nslices < 1500 && c.w > 16 * a.nslices) a.nslices *= 2;
+    a.sw = (int32_t)round_up(ceil_div(c.w, a.nslices), 16);
+  } else {
+    a.nslices = c.w >= 32 ? 8 : 1;
+    a.sw = (int32_t)round_up(ceil_div(c.w, a.nslices), 4);
+  }
+  // Two windows per workgroup once the grid would pass 16,384 workgroups:
+  // each workgroup pays a chain of dependent loads (window record, entry
+  // metadata, first gathers) before its gathers stream, which a longer entry
+  // range amortises (50,000 nodes x 256 columns: 213 -> 175 us; 20,000 x
+  // 200: 80 -> 77 us); smaller launches keep one (8,000 x 512: even).
+  a.nblk = (int32_t)d.nblk;
+  a.wpb = d.nblk * a.nslices > 16384 ? 2 : 1;
+  a.nwin = (int32_t)ceil_div(d.nblk, (int64_t)a.wpb);
   // Gather offsets in 32 bits when the input spans less than 4 GiB.
   const bool off32 = ((int64_t)(c.n - 1) * c.ld_in + c.w) * 4 < (int64_t(1) << 32);
   *vec_out = vec;
@@ -947,8 +970,9 @@ static void spmm_floor_dispatch(const SpmmArgs& a, bool off32, hipStream_t s) {
   const int units = ceil_div(a.sw, 4);  // the lane groups of spmm_dispatch
   if (units <= 4) return spmm_floor_go<4, RAG>(a, off32, s);
   if (units <= 8) return spmm_floor_go<8, RAG>(a, off32, s);
-  if (units == 10 && a.nslices == 8) return spmm_floor_go<10, RAG>(a, off32, s);
+  if (units <= 12) return spmm_floor_go<12, RAG>(a, off32, s);
   if (units <= 16) return spmm_floor_go<16, RAG>(a, off32, s);
+  if (units <= 20) return spmm_floor_go<20, RAG>(a, off32, s);
   if (units <= 32) return spmm_floor_go<32, RAG>(a, off32, s);
   return spmm_floor_go<64, RAG>(a, off32, s);
 }
