@@ -12,12 +12,17 @@
 // number of neighbours below v): deg(v) + 1 slots.  The slots of all rows
 // are laid end to end (row offsets off[i], an exclusive scan of deg + 1).
 // A slot is kept if it is the self loop or a neighbour w != v of V_s
-// (map[w] >= 0, map = full id -> position in V_s).  One exclusive scan of
-// the keep flags over the whole entry space gives every kept slot its
-// output position, and the count before row i's first slot is indptr_s[i].
+// (map[w] >= 0, map = full id -> position in V_s).  The number of keep flags
+// before it in the entry space is a kept slot's output position, and the
+// count before row i's first slot is indptr_s[i].
 // Rows come out sorted because V_s is sorted and the map keeps that order.
 // Work is split into equal slot chunks over a fixed grid, so a hub row of
 // the full graph is shared by many workgroups.
+//
+// What bounds it: launches and chains of dependent loads, not bytes.  Five
+// launches where scans of their own made nine, and the wavefront search and
+// staged rows below: 8,000 frontier-sampled nodes of a 2^17-node graph, the
+// whole call with its gathers and read-back, 141.5 -> 114.6 us.
 #include <cmath>
 
 #include "abi.hpp"
@@ -159,37 +164,134 @@ __global__ void induce_clear_kernel(int32_t* __restrict__ status,
   }
 }
 
+// Up to this many rows, each block of the offsets kernel adds up the slot
+// counts of the 256-row blocks before it (at most 1,024 of them, four loads a
+// thread): two launches from the node list to the offsets, where the general
+// scan takes five (clear, rows, three scan passes).  The subgraphs of the
+// paper's setting are far below; above, that prefix would grow with the
+// square of the rows, and the general scan is used.
+constexpr int32_t FUSED_ROWS = 256 * 1024;
+constexpr int BAD_SHIFT = 56;  // status bits of a block's rows, above its sum
+
 // Per sampled row: range and order checks, map[v] = i, deg + 1 slots and the
 // self loop's slot p_i.  Rows whose node is out of range keep the self loop
-// alone and never touch the full graph.
+// alone and never touch the full graph.  With sums, a block leaves its slot
+// count and status bits there; without, it adds the bits to *status.
 __global__ __launch_bounds__(256) void induce_rows_kernel(
     int64_t n_full, const int64_t* __restrict__ indptr,
     const int32_t* __restrict__ indices, int32_t n_s,
     const int32_t* __restrict__ nodes, int32_t* __restrict__ map,
     int32_t* __restrict__ slots, int32_t* __restrict__ pself,
-    int32_t* __restrict__ status) {
-  const int32_t i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n_s) return;
-  const int32_t v = nodes[i];
-  int bad = (v < 0 || (int64_t)v >= n_full) ? ST_RANGE : 0;
-  if (i + 1 < n_s && nodes[i + 1] <= v) bad |= ST_ORDER;
-  if (bad & ST_RANGE) {
-    slots[i] = 1;
-    pself[i] = 0;
-  } else {
-    map[v] = i;
-    const int64_t b = indptr[v];
-    const int64_t deg = indptr[v + 1] - b;
-    int64_t lo = 0, hi = deg;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (indices[b + mid] < v) lo = mid + 1;
-      else hi = mid;
+    int64_t* __restrict__ sums, int32_t* __restrict__ status) {
+  __shared__ int64_t wsum[4];
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  int bad = 0;
+  int32_t cnt = 0;
+  if (i < n_s) {
+    const int32_t v = nodes[i];
+    bad = (v < 0 || (int64_t)v >= n_full) ? ST_RANGE : 0;
+    if (i + 1 < n_s && nodes[i + 1] <= v) bad |= ST_ORDER;
+    int64_t lo = 0;
+    cnt = 1;
+    if (!(bad & ST_RANGE)) {
+      map[v] = (int32_t)i;
+      const int64_t b = indptr[v];
+      const int64_t deg = indptr[v + 1] - b;
+      int64_t hi = deg;
+      while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (indices[b + mid] < v) lo = mid + 1;
+        else hi = mid;
+      }
+      cnt = (int32_t)(deg + 1);
     }
-    slots[i] = (int32_t)(deg + 1);
+    slots[i] = cnt;
     pself[i] = (int32_t)lo;
   }
-  if (bad) atomicOr(status, bad);
+  if (!sums) {
+    if (bad) atomicOr(status, bad);
+    return;
+  }
+  int64_t s = cnt;
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    s += __shfl_xor(s, d, 64);
+    bad |= __shfl_xor(bad, d, 64);
+  }
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = s | ((int64_t)bad << BAD_SHIFT);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    constexpr int64_t M = (int64_t(1) << BAD_SHIFT) - 1;
+    int64_t t = 0, st = 0;
+    for (int k = 0; k < 4; ++k) {
+      t += wsum[k] & M;
+      st |= wsum[k] & ~M;
+    }
+    sums[blockIdx.x] = t | st;
+  }
+}
+
+// Sum over the block of 256 threads; lds: 4 int64, free again on return.
+__device__ inline int64_t block_sum(int64_t s, int64_t* lds) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = s;
+  __syncthreads();
+  s = lds[0] + lds[1] + lds[2] + lds[3];
+  __syncthreads();
+  return s;
+}
+
+// off[0 .. n_s] from the slots and the block sums of induce_rows_kernel (the
+// same blocks of 256 rows); block 0 also collects the status bits.
+__global__ __launch_bounds__(256) void induce_offsets_kernel(
+    int32_t n_s, const int32_t* __restrict__ slots, const int64_t* __restrict__ sums,
+    int64_t* __restrict__ off, int32_t* __restrict__ status) {
+  __shared__ int64_t lds[4];
+  __shared__ int32_t sbad[4];
+  constexpr int64_t M = (int64_t(1) << BAD_SHIFT) - 1;
+  const int32_t i = blockIdx.x * 256 + threadIdx.x;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int64_t before = 0;
+  for (int k = threadIdx.x; k < (int)blockIdx.x; k += 256) before += sums[k] & M;
+  before = block_sum(before, lds);
+  const int32_t cnt = i < n_s ? slots[i] : 0;
+  int64_t inc = cnt;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int64_t y = __shfl_up(inc, d, 64);
+    if (lane >= d) inc += y;
+  }
+  if (lane == 63) lds[w] = inc;
+  __syncthreads();
+  for (int k = 0; k < w; ++k) before += lds[k];
+  if (i < n_s) off[i] = before + inc - cnt;
+  if (i == n_s - 1) off[n_s] = before + inc;
+  if (blockIdx.x == 0) {
+    int bad = 0;
+    for (int k = threadIdx.x; k < (int)gridDim.x; k += 256) bad |= (int)(sums[k] >> BAD_SHIFT);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) bad |= __shfl_xor(bad, d, 64);
+    if (lane == 0) sbad[w] = bad;
+    __syncthreads();
+    if (threadIdx.x == 0) *status = sbad[0] | sbad[1] | sbad[2] | sbad[3];
+  }
+}
+
+// Row of slot e by a whole wavefront: the last row r in [lo, hi] with
+// off[r] <= e, 64 probes a step (three dependent loads for 8,000 rows, where
+// halving takes thirteen).  e is the same in every lane.
+__device__ inline int32_t row_of_wave(const int64_t* __restrict__ off, int32_t lo,
+                                      int32_t hi, int64_t e) {
+  const int lane = threadIdx.x & 63;
+  while (lo < hi) {
+    const int32_t step = (hi - lo + 63) >> 6;
+    const int64_t pos = lo + (int64_t)(lane + 1) * step;
+    const bool le = pos <= hi && off[pos] <= e;
+    lo += __popcll(__ballot(le)) * step;
+    hi = std::min(hi - lo, step - 1) + lo;
+  }
+  return lo;
 }
 
 // Row of slot e: the last row r in [lo, hi] with off[r] <= e.
@@ -214,12 +316,22 @@ struct EntryArgs {
   const int64_t* off;  // n_s + 1
 };
 
-// Column (position in V_s) that slot k of row i keeps, or -1.
-__device__ inline int32_t slot_target(const EntryArgs& a, int32_t i, int64_t k) {
-  const int32_t p = a.pself[i];
-  if (k == p) return i;
+struct RowInfo {
+  int64_t begin;  // of v's row in the full graph (0 if v is out of range)
+  int32_t v, p;   // full id, slot of the self loop
+};
+
+__device__ inline RowInfo row_info(const EntryArgs& a, int32_t i) {
   const int32_t v = a.nodes[i];
-  const int32_t w = a.indices[a.indptr[v] + (k - (k > p ? 1 : 0))];
+  return RowInfo{v >= 0 && (int64_t)v < a.n_full ? a.indptr[v] : 0, v, a.pself[i]};
+}
+
+// Column (position in V_s) that slot k of row i keeps, or -1.
+__device__ inline int32_t slot_target(const EntryArgs& a, const RowInfo& q, int32_t i,
+                                      int64_t k) {
+  const int32_t p = q.p, v = q.v;
+  if (k == p) return i;
+  const int32_t w = a.indices[q.begin + (k - (k > p ? 1 : 0))];
   if (w == v) return -1;  // a loop stored in the full graph counts once
   if (w < 0 || (int64_t)w >= a.n_full) return -1;
   return a.map[w];
@@ -233,9 +345,10 @@ __device__ inline bool chunk_of(const EntryArgs& a, int64_t& start, int64_t& end
   start = (int64_t)blockIdx.x * chunk;
   end = std::min(E, start + chunk);
   if (start >= end) return false;
-  if (threadIdx.x == 0) {
-    lds[0] = row_of(a.off, 0, a.n_s - 1, start);
-    lds[1] = row_of(a.off, lds[0], a.n_s - 1, end - 1);
+  const int w = threadIdx.x >> 6;
+  if (w < 2) {
+    const int32_t r = row_of_wave(a.off, 0, a.n_s - 1, w == 0 ? start : end - 1);
+    if ((threadIdx.x & 63) == 0) lds[w] = r;
   }
   __syncthreads();
   r_lo = lds[0];
@@ -243,48 +356,60 @@ __device__ inline bool chunk_of(const EntryArgs& a, int64_t& start, int64_t& end
   return true;
 }
 
-// The chunk's row offsets off[r_lo .. r_hi + 1], staged in LDS when they
-// fit, so that each slot finds its row without global reads.
+// The chunk's row offsets off[r_lo .. r_hi + 1] and its rows' places in the
+// full graph, staged in LDS when they fit, so that a slot's only global reads
+// are the neighbour and its map entry (two dependent loads instead of four).
 constexpr int ROW_CACHE = 512;
 
+struct RowStage {
+  int64_t off[ROW_CACHE + 1];
+  RowInfo info[ROW_CACHE];
+};
+
 struct Rows {
-  const int64_t* off;  // LDS copy (relative to r_lo) or the global array
+  const int64_t* off;   // LDS copy (relative to r_lo) or the global array
+  const RowInfo* info;  // LDS copy, or NULL
   int32_t lo, hi, base;
 };
 
 __device__ inline Rows stage_rows(const EntryArgs& a, int32_t r_lo, int32_t r_hi,
-                                  int64_t* s_off) {
-  const int32_t cnt = r_hi - r_lo + 2;
-  if (cnt > ROW_CACHE + 1) return Rows{a.off, r_lo, r_hi, 0};
-  for (int32_t k = threadIdx.x; k < cnt; k += 256) s_off[k] = a.off[r_lo + k];
+                                  RowStage& s) {
+  const int32_t rows = r_hi - r_lo + 1;
+  if (rows > ROW_CACHE) return Rows{a.off, nullptr, r_lo, r_hi, 0};
+  for (int32_t k = threadIdx.x; k <= rows; k += 256) {
+    s.off[k] = a.off[r_lo + k];
+    if (k < rows) s.info[k] = row_info(a, r_lo + k);
+  }
   __syncthreads();
-  return Rows{s_off, 0, r_hi - r_lo, r_lo};
+  return Rows{s.off, s.info, 0, r_hi - r_lo, r_lo};
 }
 
-// (row, slot within the row) of entry e
-__device__ inline int32_t row_in(const Rows& R, int64_t e, int64_t& k) {
+// Row i and column of entry e (-1: not kept); k: its slot within the row.
+__device__ inline int32_t entry_target(const EntryArgs& a, const Rows& R, int64_t e,
+                                       int32_t& i, int64_t& k) {
   const int32_t r = row_of(R.off, R.lo, R.hi, e);
   k = e - R.off[r];
-  return r + R.base;
+  i = r + R.base;
+  return R.info ? slot_target(a, R.info[r], i, k) : slot_target(a, row_info(a, i), i, k);
 }
 
 __global__ __launch_bounds__(256) void induce_count_kernel(EntryArgs a,
                                                            int64_t* __restrict__ counts) {
   __shared__ int32_t rows[2];
   __shared__ int32_t wsum[4];
-  __shared__ int64_t s_off[ROW_CACHE + 1];
+  __shared__ RowStage stage;
   int64_t start, end;
   int32_t r_lo, r_hi;
   if (!chunk_of(a, start, end, r_lo, r_hi, rows)) {
     if (threadIdx.x == 0) counts[blockIdx.x] = 0;
     return;
   }
-  const Rows R = stage_rows(a, r_lo, r_hi, s_off);
+  const Rows R = stage_rows(a, r_lo, r_hi, stage);
   int32_t c = 0;
   for (int64_t e = start + threadIdx.x; e < end; e += 256) {
+    int32_t i;
     int64_t k;
-    const int32_t i = row_in(R, e, k);
-    c += slot_target(a, i, k) >= 0;
+    c += entry_target(a, R, e, i, k) >= 0;
   }
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) c += __shfl_xor(c, d, 64);
@@ -293,34 +418,46 @@ __global__ __launch_bounds__(256) void induce_count_kernel(EntryArgs a,
   if (threadIdx.x == 0) counts[blockIdx.x] = (int64_t)wsum[0] + wsum[1] + wsum[2] + wsum[3];
 }
 
-// Writes the kept slots at their scanned positions and indptr_s; block 0
-// also writes the total and checks it against the capacity.
+// Writes the kept slots at their positions and indptr_s.  A block adds up the
+// counts of the chunks before its own (four loads a thread, instead of a scan
+// launch between the two passes); block 0, which always has slots, also
+// writes the total and checks it against the capacity.
 __global__ __launch_bounds__(256) void induce_fill_kernel(
-    EntryArgs a, const int64_t* __restrict__ boff, int64_t capacity,
+    EntryArgs a, const int64_t* __restrict__ counts, int64_t capacity,
     int32_t* __restrict__ sub_indptr, int32_t* __restrict__ sub_indices,
     int64_t* __restrict__ nnz_out, int32_t* __restrict__ status) {
   __shared__ int32_t rows[2];
   __shared__ int32_t wcnt[4];
-  __shared__ int64_t s_off[ROW_CACHE + 1];
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    const int64_t total = boff[CHUNK_BLOCKS];
-    *nnz_out = total;
-    sub_indptr[a.n_s] = (int32_t)std::min<int64_t>(total, INT32_MAX);
-    if (total > capacity || total > INT32_MAX) atomicOr(status, ST_CAPACITY);
-  }
+  __shared__ RowStage stage;
+  __shared__ int64_t csum[4];
   int64_t start, end;
   int32_t r_lo, r_hi;
   if (!chunk_of(a, start, end, r_lo, r_hi, rows)) return;
-  const Rows R = stage_rows(a, r_lo, r_hi, s_off);
+  const Rows R = stage_rows(a, r_lo, r_hi, stage);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int64_t run = boff[blockIdx.x];
+  int64_t run = 0, all = 0;
+#pragma unroll
+  for (int q = 0; q < CHUNK_BLOCKS / 256; ++q) {
+    const int c = q * 256 + threadIdx.x;
+    const int64_t x = counts[c];
+    all += x;
+    if (c < (int)blockIdx.x) run += x;
+  }
+  run = block_sum(run, csum);
+  if (blockIdx.x == 0) {
+    const int64_t total = block_sum(all, csum);
+    if (threadIdx.x == 0) {
+      *nnz_out = total;
+      sub_indptr[a.n_s] = (int32_t)std::min<int64_t>(total, INT32_MAX);
+      if (total > capacity || total > INT32_MAX) atomicOr(status, ST_CAPACITY);
+    }
+  }
   for (int64_t base = start; base < end; base += 256) {
     const int64_t e = base + threadIdx.x;
     int32_t i = 0, t = -1;
     int64_t k = -1;
     if (e < end) {
-      i = row_in(R, e, k);
-      t = slot_target(a, i, k);
+      t = entry_target(a, R, e, i, k);
     }
     const uint64_t m = __ballot(t >= 0);
     const int32_t below = __popcll(m & ((1ull << lane) - 1ull));
@@ -391,7 +528,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(
 }
 
 struct InduceLayout {
-  size_t off_slots, off_pself, off_off, off_tmp, off_counts, off_boff, total;
+  size_t off_slots, off_pself, off_off, off_tmp, off_counts, off_sums, total;
 };
 
 InduceLayout induce_layout(int32_t n_s) {
@@ -408,8 +545,8 @@ InduceLayout induce_layout(int32_t n_s) {
   p += round_up((size_t)tiles * 2 * 8, 256);
   o.off_counts = p;
   p += round_up((size_t)CHUNK_BLOCKS * 8, 256);
-  o.off_boff = p;
-  p += round_up((size_t)(CHUNK_BLOCKS + 1) * 8, 256);
+  o.off_sums = p;
+  p += round_up((size_t)(FUSED_ROWS / 256 + 1) * 8, 256);
   o.total = p;
   return o;
 }
@@ -460,7 +597,9 @@ gnn_status gnn_induce_subgraph(int64_t n_full, int64_t nnz_full,
     }
   }
   timer_begin(GNN_K_INDUCE, stream);
-  induce_clear_kernel<<<1, 64, 0, stream>>>(status_out, nnz_out, sub_indptr, n_s);
+  const bool fused = n_s > 0 && n_s <= FUSED_ROWS;
+  if (!fused)
+    induce_clear_kernel<<<1, 64, 0, stream>>>(status_out, nnz_out, sub_indptr, n_s);
   if (n_s == 0) {  // empty node set: indptr_s = {0}, nnz 0, status 0
     timer_end(GNN_K_INDUCE, 0.0, stream);
     GNN_HIP(hipGetLastError());
@@ -472,16 +611,22 @@ gnn_status gnn_induce_subgraph(int64_t n_full, int64_t nnz_full,
   int64_t* off = reinterpret_cast<int64_t*>(ws + o.off_off);
   int64_t* tmp = reinterpret_cast<int64_t*>(ws + o.off_tmp);
   int64_t* counts = reinterpret_cast<int64_t*>(ws + o.off_counts);
-  int64_t* boff = reinterpret_cast<int64_t*>(ws + o.off_boff);
-  induce_rows_kernel<<<(unsigned)ceil_div(n_s, 256), 256, 0, stream>>>(
-      n_full, indptr, indices, n_s, nodes, map, slots, pself, status_out);
+  int64_t* sums = reinterpret_cast<int64_t*>(ws + o.off_sums);
+  const unsigned row_blocks = (unsigned)ceil_div(n_s, 256);
+  induce_rows_kernel<<<row_blocks, 256, 0, stream>>>(n_full, indptr, indices, n_s, nodes, map,
+                                                     slots, pself, fused ? sums : nullptr,
+                                                     status_out);
   GNN_HIP(hipGetLastError());
-  GNN_HIP(scan_exclusive<int32_t>(n_s, slots, off, tmp, stream));
+  if (fused) {
+    induce_offsets_kernel<<<row_blocks, 256, 0, stream>>>(n_s, slots, sums, off, status_out);
+    GNN_HIP(hipGetLastError());
+  } else {
+    GNN_HIP(scan_exclusive<int32_t>(n_s, slots, off, tmp, stream));
+  }
   EntryArgs a{n_s, n_full, indptr, indices, nodes, map, pself, off};
   induce_count_kernel<<<CHUNK_BLOCKS, 256, 0, stream>>>(a, counts);
   GNN_HIP(hipGetLastError());
-  GNN_HIP(scan_exclusive<int64_t>(CHUNK_BLOCKS, counts, boff, tmp, stream));
-  induce_fill_kernel<<<CHUNK_BLOCKS, 256, 0, stream>>>(a, boff, capacity, sub_indptr,
+  induce_fill_kernel<<<CHUNK_BLOCKS, 256, 0, stream>>>(a, counts, capacity, sub_indptr,
                                                        sub_indices, nnz_out, status_out);
   GNN_HIP(hipGetLastError());
   induce_values_kernel<<<(unsigned)ceil_div(n_s, 4), 256, 0, stream>>>(

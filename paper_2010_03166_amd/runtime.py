@@ -121,8 +121,11 @@ class FullGraphDevice:
             torch.from_numpy(np.ascontiguousarray(X, np.float32)).to(device)
         self.labels = None if labels is None else \
             torch.from_numpy(np.ascontiguousarray(labels, np.float32)).to(device)
-        self.nnz_out = torch.zeros(1, dtype=torch.int64, device=device)
-        self.status = torch.zeros(1, dtype=torch.int32, device=device)
+        # side by side, read back by one copy (the status word's upper half
+        # stays 0)
+        self.meta = torch.zeros(2, dtype=torch.int64, device=device)
+        self.nnz_out = self.meta[:1]
+        self.status = self.meta.view(torch.int32)[2:3]
 
     def capacity(self, nodes: np.ndarray) -> int:
         """Entries the induced subgraph of `nodes` can hold at most."""
@@ -156,7 +159,7 @@ class FullGraphDevice:
             Ts = torch.empty((n_s, C), device=self.device)
             G.gnn_gather_rows(n_s, nd, C, self.labels, self.labels.stride(0), self.n, Ts,
                               C, stream)
-        st, nnz = int(self.status.item()), int(self.nnz_out.item())
+        nnz, st = self.meta.tolist()
         if st:
             raise ValueError("gnn_induce_subgraph status %d (1: id out of range, 2: ids "
                              "not ascending, 4: over capacity)" % st)

@@ -4,6 +4,8 @@ ABI.  Structure (row pointers, column indices) bit-exact; values are the
 correctly rounded fp32 of the oracle's double values up to one rounding of
 the square root: max relative error 1e-7.
 """
+import functools
+
 import numpy as np
 import pytest
 import torch
@@ -20,6 +22,15 @@ FULL = {
     "kron12": synth.kronecker_graph(12, 16.0, 1),
     "kron15": synth.kronecker_graph(15, 16.0, 2),
 }
+
+
+@functools.lru_cache(maxsize=None)
+def SPARSE():
+    """600,000 nodes, most of them isolated, and one hub."""
+    rng = np.random.default_rng(8)
+    u, v = rng.integers(0, 600000, (2, 50000))
+    hub = rng.integers(0, 600000, 3000)
+    return synth.full_from_pairs(600000, np.r_[u, np.full(3000, 7)], np.r_[v, hub])
 
 
 def _buf(nbytes):
@@ -273,3 +284,17 @@ def test_pipeline_matches_serial_iterations():
     # the subgraphs differ in size from one iteration to the next
     sizes = {len(G.gnn_frontier_sample(full, 60, 700, 2.0, 16, 9, k)) for k in range(6)}
     assert len(sizes) > 1
+
+
+@pytest.mark.parametrize("n_s", [1, 255, 256, 257, 4096, 262144, 262145, 600000])
+def test_induce_row_block_edges(n_s):
+    """Edges of the blocks of 256 rows, the last size whose offsets come from
+    block sums and the first one scanned, and chunks of more rows (600,000 /
+    1,024 > 512) than the fill keeps in LDS."""
+    full = SPARSE()
+    nodes = np.sort(np.random.default_rng(n_s).choice(full.n, n_s, replace=False)).astype(np.int32)
+    check_parity(full, nodes, G.GNN_NORM_ROW, run_induce(full, nodes, G.GNN_NORM_ROW))
+    # ids out of order in the last rows: reported, whatever block they are in
+    if n_s > 1:
+        nodes[-2:] = nodes[-2:][::-1].copy()
+        assert run_induce(full, nodes, G.GNN_NORM_ROW)["status"] & 2
