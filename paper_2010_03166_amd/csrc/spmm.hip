@@ -901,24 +901,23 @@ static SpmmArgs spmm_args(const SpmmCall& c, bool* vec_out, bool* off32_out) {
                    (c.epilogue != SPMM_ADD || vec4_ok(c.res, c.ld_res)) &&
                    (!c.mask || vec4_ok(c.mask, c.ld_mask));
   // Column slices.  Each slice walks all entries (index, value, row: 12 bytes
-  // and their shuffles and row closings), so few, wide slices cost least per
-  // gathered byte; many, narrow ones keep the gathered rows in L2 and more
-  // workgroups in flight.  Measured best (us; 8 slices of a multiple of 4
-  // columns before): up to 64 columns one slice (50,000 x 64: 50, before
-  // 209), two up to 128 (20,000 x 128: 25, 65) and, from 1,500 windows on, to
-  // 256 (20,000 x 200: 39, 66; four slices 47) and four to 512 (50,000 x
-  // 300: 177, 258); smaller graphs take four up to 320 columns (8,000 x 300:
-  // 18.6, 23.8) and then eight, and twice as many while their workgroups
-  // would leave the chip short of them (8,000 x 128: 14.3 in two slices, 12.3
-  // in four).  Slices are a multiple of 16 columns wide, so that they start
-  // on 64 bytes wherever rows do and a gathered slice row touches no line
-  // more than it fills (8,000 x 602: eight of 80 columns 27.7 us, sixteen of
-  // 40 41.1).  Rows off 16-byte alignment (float lanes) keep eight slices.
+  // and their shuffles and row closings), so slices narrower than 32 columns
+  // cost more than they bring (two slices up to 64 columns, four up to 128);
+  // wider ones put a hub row, which one workgroup owns, on fewer lane groups,
+  // and its time then sets the launch's.  On power-law graphs without a degree
+  // cap (us in two / four / eight slices; eight of a multiple of 4 columns
+  // before): 20,000 x 128 99 / 61 / 61 (64), 50,000 x 128 243 / 147 / 205
+  // (214), 20,000 x 200 189 / 106 / 73 (84), 20,000 x 512 378 / 199 / 113
+  // (114), 50,000 x 340 934 / 481 / 285 (385).  Graphs whose largest row is
+  // short would take fewer (20,000 x 200 at most 1,000 entries a row: 39 in
+  // two), but the degrees are not known here.  Small graphs take twice as many
+  // while their workgroups would leave the chip short of them.  Slices are a
+  // multiple of 16 columns wide, so that they start on 64 bytes wherever rows
+  // do and a gathered slice row touches no line more than it fills (8,000 x
+  // 602: eight of 80 columns 27.7 us, sixteen of 40 41.1).  Rows off 16-byte
+  // alignment (float lanes) keep eight slices.
   if (vec) {
-    const bool many = d.nblk >= 1500;
-    a.nslices = c.w <= 64 ? 1
-                : c.w <= (many ? 256 : 128) ? 2
-                : c.w <= (many ? 512 : 320) ? 4 : 8;
+    a.nslices = c.w <= 32 ? 1 : c.w <= 64 ? 2 : c.w <= 128 ? 4 : 8;
     while (a.nslices < 8 && d.nblk * a.nslices < 1500 && c.w > 16 * a.nslices) a.nslices *= 2;
     a.sw = (int32_t)round_up(ceil_div(c.w, a.nslices), 16);
   } else {
