@@ -1833,12 +1833,13 @@ static Shape gemm_shape(const GemmBatch& b) {
     // 608: 252 tiles of 64 26 us, split along K 32 + 10; 20000 x 1024, K =
     // 200: 1,256 whole tiles 75 us, stream-K 70 + 27.
     // Where the rule above shares tiles and whole ones are faster, CHAIN
-    // keeps the result as accurate as the partial sums; not beyond 512 tiles,
-    // where few are shared: those stay shared over more than 640 k.
+    // keeps the result as accurate as the partial sums, however many tiles
+    // there are: stream-K over 512 blocks cuts up to 511 of them (relative
+    // error at 6600 x 1536, K = 600, 624 tiles: shared 3.2e-7, whole 3.7e-7,
+    // whole with CHAIN 9.6e-8; 20000 x 512, K = 400: 2.6e-7, 2.9e-7, 8.3e-8).
     const double s1[3] = {0.98, 1.26, 1.5}, s2[3] = {1.4, 1.9, 2.5}, fixed = 8.0;
     const bool shared = s.nblocks != s.tiles;
-    const bool chain = shared && s.tiles <= slots;
-    if (shared && !chain && s.ktiles > 20) return s;
+    const bool chain = shared;
     const int parts = s.splits;
     auto per_stage = [&](int i, int blocks) { return blocks <= NUM_CU ? s1[i] : s2[i]; };
     auto whole_stage = [&](int i, int blocks) {

@@ -56,3 +56,23 @@ def test_split_planes(M, N, K, ta, tb, pad):
     err = np.abs(got[:, :N] - ad @ bd)
     bound = (12 * -(-K // 32) + 8) * 2.0 ** -23 * (np.abs(ad) @ np.abs(bd))
     assert (err <= bound).all(), float((err / bound).max())
+
+
+@pytest.mark.parametrize("M,N,K,shared,unbroken", [
+    (6600, 1536, 600, 3.16e-7, 3.65e-7), (20000, 512, 400, 2.55e-7, 2.94e-7),
+    (20000, 1024, 602, 3.48e-7, 3.69e-7)])
+def test_whole_tiles_for_shared_ones_keep_partial_sums(M, N, K, shared, unbroken):
+    """More than 512 tiles of 128 x 128, where the general work split shares
+    tiles over blocks.  Relative 2-norm errors measured: `shared` with its
+    partial sums, `unbroken` with all of K in one chain of the matrix cores,
+    which truncate what they shift out (below 1e-7 when the sums begin anew
+    every 32 k).  The limit lies halfway between the two."""
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn((M, -(-K // 4) * 4), device="cuda", generator=gen)
+    B = torch.randn((K, N), device="cuda", generator=gen)
+    C = torch.empty((M, N), device="cuda")
+    ws = torch.empty(max(G.gnn_gemm_workspace_bytes(M, N, K), 256), dtype=torch.uint8,
+                     device="cuda")
+    G.gnn_gemm(0, 0, M, N, K, A, A.stride(0), B, N, C, N, 0, ws)
+    ref = A[:, :K].double() @ B.double()
+    assert ((C.double() - ref).norm() / ref.norm()).item() < (shared + unbroken) / 2
