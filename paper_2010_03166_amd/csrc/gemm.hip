@@ -1754,6 +1754,7 @@ struct Shape {
   int64_t iters;
   int nblocks;
   int splits;
+  int too_big;  // more tiles than the 32-bit tile numbers hold: no launch
   int bn;     // tile width (64, 96 or 128 with planes, else 128)
   int chain;  // with planes: CHAIN
 };
@@ -1771,6 +1772,8 @@ static Shape gemm_shape(const GemmBatch& b) {
   s.tiles_m = (int)ceil_div(M, BM);
   s.tiles_n0 = (int)ceil_div(b.p[0].N, BN);
   s.tiles_n = s.tiles_n0 + (b.nprob > 1 ? (int)ceil_div(b.p[1].N, BN) : 0);
+  s.too_big = (int64_t)s.tiles_m * s.tiles_n > INT32_MAX;
+  if (s.too_big) return s;  // (the size query of such a call asks for nothing)
   s.tiles = s.tiles_m * s.tiles_n;
   for (int i = 0; i < b.nprob; ++i) {
     const GemmProblem& p = b.p[i];
@@ -1852,6 +1855,7 @@ static Shape gemm_shape(const GemmBatch& b) {
       c.bn = 64 + 32 * i;
       c.tiles_n0 = (int)ceil_div(b.p[0].N, c.bn);
       c.tiles_n = c.tiles_n0 + (b.nprob > 1 ? (int)ceil_div(b.p[1].N, c.bn) : 0);
+      if ((int64_t)c.tiles_m * c.tiles_n > INT32_MAX) continue;
       c.tiles = c.tiles_m * c.tiles_n;
       c.iters = (int64_t)c.tiles * c.ktiles;
       c.splits = 1;
@@ -1944,6 +1948,7 @@ hipError_t gemm_launch(const GemmBatch& b, void* workspace, size_t ws_bytes,
         if (b.p[i].seg[k].K > 0 && !b.p[i].seg[k].Bp) return hipErrorInvalidValue;
   }
   const Shape sh = gemm_shape(b);
+  if (sh.too_big) return hipErrorInvalidValue;
   if (sh.tiles == 0) return pending ? gemm_flush(*pending, s) : hipSuccess;
   GemmKArgs g;
   memset(&g, 0, sizeof(g));

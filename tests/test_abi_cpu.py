@@ -6,6 +6,8 @@ and reject bad arguments synchronously, before anything is enqueued.
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -107,6 +109,28 @@ def test_size_queries(lib):
     assert G.gnn_gemm_workspace_bytes(8000, 1024, 602) == 3 * 38 * 1024 * 16 * 2
     assert G.gnn_gemm_workspace_bytes(602, 512, 8000) > 0  # split along K
     assert G.gnn_spmm_workspace_bytes(c, 512) == 0  # one kernel, no partials
+
+
+def test_size_queries_of_sizes_past_32_bit_tile_counts():
+    """Products of more tiles than 32 bits number: the size queries return
+    (in a child process: a division by a wrapped tile count would end it)."""
+    code = (
+        "from paper_2010_03166_amd import gnnprop as G\n"
+        "top = 2 ** 31 - 1\n"
+        "for m, n in ((top, 16384), (top, 16320), (2 ** 30, 32768), (top, 8192), (top, top)):\n"
+        "    for k in (64, 2048, top):\n"
+        "        assert G.gnn_gemm_workspace_bytes(m, n, k) >= 0\n"
+        "c = G.make_csr(top, 16, 0x1000, 0x2000, 0x3000, None, None)\n"
+        "for f, h in ((16384, 8192), (8192, 16384), (16384, 16384)):\n"
+        "    for flags in (0, G.GNN_FLAG_BF16, G.GNN_FLAG_F32_MFMA):\n"
+        "        l = G.make_layer(f, h, f, 3 * h, f, 0, flags)\n"
+        "        assert G.gnn_prop_workspace_bytes(c, l) > 0\n"
+        "        assert G.gnn_gcn_workspace_bytes(c, l) > 0\n"
+        "        assert G.gnn_gat_workspace_bytes(c, l) > 0\n"
+        "        assert G.gnn_mixhop_workspace_bytes(c, l, 2) > 0\n"
+        "    assert G.gnn_classifier_workspace_bytes(top, f, h) > 0\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
 
 
 def _st(fn, *args):
