@@ -1966,8 +1966,7 @@ hipError_t gemm_launch(const GemmBatch& b, void* workspace, size_t ws_bytes,
   bool va = true, vb = true;
   // 4 consecutive elements per load: 16 bytes (fp32) or 8 (bf16 storage)
   auto vec_ok = [](const void* p, int64_t ld, bool h) {
-    return ld < (1 << 23) &&
-           (h ? (reinterpret_cast<uintptr_t>(p) % 8 == 0 && ld % 4 == 0) : vec4_ok(p, ld));
+    return h ? (reinterpret_cast<uintptr_t>(p) % 8 == 0 && ld % 4 == 0) : vec4_ok(p, ld);
   };
   for (int i = 0; i < b.nprob; ++i) {
     g.p[i] = b.p[i];
@@ -1978,7 +1977,9 @@ hipError_t gemm_launch(const GemmBatch& b, void* workspace, size_t ws_bytes,
     g.ktiles0[i] = sh.kt0[i];
     const GemmProblem& p = g.p[i];
     for (int k = 0; k < p.nseg; ++k) {
-      va = va && vec_ok(p.seg[k].A, p.seg[k].lda, b.a16 != 0);
+      // (gemm_planes_kernel: 32-bit byte offsets over the tile's rows of A)
+      va = va && vec_ok(p.seg[k].A, p.seg[k].lda, b.a16 != 0) &&
+           (!b.b_planes || p.seg[k].lda < (1 << 23));
       vb = vb && vec_ok(p.seg[k].B, p.seg[k].ldb, b.b16 != 0);
     }
   }

@@ -1,0 +1,52 @@
+"""Launches on the two sides of a rule's edge, or of one work split and the
+next, must not differ in time by more than their work does.  Times are the
+smallest of several replays of captured calls; each limit lies between what
+both sides measured with and without the fault that the test names."""
+import pytest
+import torch
+
+from paper_2010_03166_amd import gnnprop as G
+
+pytestmark = pytest.mark.gpu
+
+
+def best_us(call, reps=8, rounds=7):
+    """Time of one of `reps` captured calls, the best of `rounds` replays."""
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        for _ in range(reps):
+            call()
+    graph.replay()
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = float("inf")
+    for _ in range(rounds):
+        a.record()
+        graph.replay()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / reps * 1e3)
+    return best
+
+
+def gemm_us(ta, tb, M, N, K, flags=0, **kw):
+    pad = lambda w: -(-w // 4) * 4
+    A = torch.randn((K, pad(M)) if ta else (M, pad(K)), device="cuda")
+    B = torch.randn((N, pad(K)) if tb else (K, pad(N)), device="cuda")
+    C = torch.empty((M, pad(N)), device="cuda")
+    ws = torch.empty(max(G.gnn_gemm_workspace_bytes(M, N, K), 256), dtype=torch.uint8,
+                     device="cuda")
+    return best_us(lambda: G.gnn_gemm(ta, tb, M, N, K, A, A.stride(0), B, B.stride(0), C,
+                                      C.stride(0), flags, ws), **kw)
+
+
+def test_long_rows_keep_float4_loads():
+    """fp32 matrix cores, op(A) = A^T of 2^23 columns and of a few more: 10 %
+    slower where the 32-bit offsets of another kernel decided (7 to 15 % over
+    the kernels that index in 64 bits)."""
+    below, above = (gemm_us(1, 0, (1 << 23) + d, 64, 64, G.GNN_FLAG_F32_MFMA, reps=2)
+                    for d in (-8, 8))
+    assert above < 1.05 * below, (below, above)
