@@ -1553,20 +1553,22 @@ __global__ __launch_bounds__(256, 2) void gemm_planes_kernel(GemmKArgs g, GemmKA
       }
     };
 
-    // Stages [kbeg, kf) are full: pipelined path, no guards (rows past M
-    // repeat the last one; loads past the end repeat the last stage, never
-    // used).
-    int kf = kbeg;
-    if (va && (A_KC || m0 + BM <= M)) {
-      const int f0 = K0 / BKP, e1 = kt0 + K1 / BKP;
-      if (kbeg < f0)
-        kf = min(kend, f0 == kt0 ? e1 : f0);
-      else if (kbeg >= kt0 && kbeg < e1)
-        kf = min(kend, e1);
-    }
-    if (kf > kbeg) {
+    // The full stages of both K segments: pipelined path, no guards (rows past
+    // M repeat the last one; loads past the end repeat the last stage, never
+    // used).  Numbered without the stage that a first segment of partial depth
+    // ends in (f0), which comes after them: stage v is v or, from f0 on, v + 1.
+    const bool full = va && (A_KC || m0 + BM <= M);
+    const int f0 = K0 / BKP, e1 = kt0 + K1 / BKP;
+    const int gap = kt0 - f0;  // 0 or 1
+    const int va0 = kbeg - (kbeg > f0 ? gap : 0);
+    const int ke = min(kend, e1);
+    const int va1 = full ? max(va0, ke - (ke > f0 ? gap : 0)) : va0;
+    if (va1 > va0) {
+      auto stage = [&](int v) {
+        v = min(v, va1 - 1);
+        return v >= f0 ? v + gap : v;
+      };
       auto load_full = [&](Raw& r, int ks) {
-        ks = min(ks, kf - 1);
         const bool s1 = ks >= kt0;
         const int k0 = (s1 ? ks - kt0 : ks) * BKP;
         const float* A = s1 ? A1p : A0p;
@@ -1581,39 +1583,42 @@ __global__ __launch_bounds__(256, 2) void gemm_planes_kernel(GemmKArgs g, GemmKA
       };
       BFr b0, b1;
       Raw r;
-      auto step = [&](int k, const uint32_t* as, uint32_t* as_n, const BFr& bc, BFr& bn) {
+      auto step = [&](int v, const uint32_t* as, uint32_t* as_n, const BFr& bc, BFr& bn) {
         AFr a;
-        __syncthreads();  // stage k stored; stage k - 1's fragments all read
+        __syncthreads();  // stage v stored; stage v - 1's fragments all read
         read_a(a, as);
-        store_op(as_n, r);  // stage k + 1
-        load_full(r, k + 2);
-        load_b(bn, min(k + 1, kf - 1), true);
+        store_op(as_n, r);  // stage v + 1
+        load_full(r, stage(v + 2));
+        load_b(bn, stage(v + 1), true);
         products(a, bc);
       };
-      load_full(r, kbeg);
-      load_b(b0, kbeg, true);
+      load_full(r, stage(va0));
+      load_b(b0, stage(va0), true);
       store_op(As0, r);
-      load_full(r, kbeg + 1);
-      for (int k = kbeg; k < kf; k += 2) {
-        step(k, As0, As1, b0, b1);
-        if (k + 1 >= kf) break;
-        step(k + 1, As1, As0, b1, b0);
+      load_full(r, stage(va0 + 1));
+      for (int v = va0; v < va1; v += 2) {
+        step(v, As0, As1, b0, b1);
+        if (v + 1 >= va1) break;
+        step(v + 1, As1, As0, b1, b0);
       }
       __syncthreads();
     }
 
-    // Remaining stages (partial K; unaligned rows): guarded loads, one stage
-    // in registers ahead.
-    if (kf < kend) {
+    // Remaining stages (the partial ones; all of them with unaligned rows):
+    // guarded loads, one stage in registers ahead.
+    const bool part0 = gap && kbeg <= f0 && f0 < kend;
+    const int rest = full ? (int)part0 + (int)(kbeg <= e1 && e1 < kend) : kend - kbeg;
+    if (rest > 0) {
+      auto stage = [&](int i) { return !full ? kbeg + i : i == 0 && part0 ? f0 : e1; };
       Raw r;
-      load_slice(r, kf);
-      for (int ks = kf; ks < kend; ++ks) {
+      load_slice(r, stage(0));
+      for (int i = 0; i < rest; ++i) {
         AFr a;
         BFr b;
-        load_b(b, ks, false);
+        load_b(b, stage(i), false);
         store_op(As0, r);
         __syncthreads();
-        if (ks + 1 < kend) load_slice(r, ks + 1);
+        if (i + 1 < rest) load_slice(r, stage(i + 1));
         read_a(a, As0);
         products(a, b);
         __syncthreads();

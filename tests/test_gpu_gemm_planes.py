@@ -11,6 +11,7 @@ import pytest
 import torch
 
 from paper_2010_03166_amd import gnnprop as G
+from paper_2010_03166_amd import runtime, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -76,3 +77,33 @@ def test_whole_tiles_for_shared_ones_keep_partial_sums(M, N, K, shared, unbroken
     G.gnn_gemm(0, 0, M, N, K, A, A.stride(0), B, N, C, N, 0, ws)
     ref = A[:, :K].double() @ B.double()
     assert ((C.double() - ref).norm() / ref.norm()).item() < (shared + unbroken) / 2
+
+
+@pytest.mark.parametrize("h", [16, 31, 32, 48, 80, 97, 208])
+@pytest.mark.parametrize("n,f", [(640, 256), (1000, 601), (8003, 300)])
+def test_two_segment_input_gradient(n, f, h):
+    """dX = G_s W_self^T + T W_neigh^T in one launch, K segments of every
+    depth within a stage of 32 (on the identity graph T = G_n).  Bound as
+    above, over the stages of both segments."""
+    dg = runtime.DeviceGraph(synth.identity_graph(n))
+    dg.prepare()
+    gen = torch.Generator().manual_seed(n + f + h)
+    rows = lambda w: torch.full((n, -(-w // 16) * 16), float("nan"), device="cuda")[:, :w]
+    X, Y, dY, dX = rows(f), rows(2 * h), rows(2 * h), rows(f)
+    dY.copy_(torch.randn((n, 2 * h), generator=gen))
+    X.copy_(torch.randn((n, f), generator=gen))
+    Ws, Wn = (torch.randn((f, h), generator=gen).cuda() for _ in range(2))
+    dWs, dWn = torch.empty_like(Ws), torch.empty_like(Wn)
+    lay = G.make_layer(f, h, X.stride(0), Y.stride(0), dX.stride(0), 2, G.GNN_FLAG_DY_MASKED)
+    csr = dg.struct()
+    saved, ws = (torch.empty(max(b, 256), dtype=torch.uint8, device="cuda") for b in
+                 (G.gnn_prop_saved_bytes(csr, lay), G.gnn_prop_workspace_bytes(csr, lay)))
+    fwd = G.make_layer(f, h, X.stride(0), Y.stride(0), dX.stride(0), 2, 0)
+    G.gnn_prop_fwd(csr, fwd, X, Ws, Wn, None, None, Y, saved, ws)
+    G.gnn_prop_bwd(csr, lay, X, Ws, Wn, Y, dY, saved, dX, dWs, dWn, None, None, ws)
+    torch.cuda.synchronize()
+    g = dY.cpu().double()
+    w = torch.cat([Ws, Wn], 1).cpu().double()
+    err = (dX.cpu().double() - g @ w.T).abs()
+    bound = (24 * -(-h // 32) + 8) * 2.0 ** -23 * (g.abs() @ w.abs().T)
+    assert (err <= bound).all(), float((err / bound).max())

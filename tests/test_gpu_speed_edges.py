@@ -2,10 +2,12 @@
 next, must not differ in time by more than their work does.  Times are the
 smallest of several replays of captured calls; each limit lies between what
 both sides measured with and without the fault that the test names."""
+import numpy as np
 import pytest
 import torch
 
 from paper_2010_03166_amd import gnnprop as G
+from paper_2010_03166_amd import runtime, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -50,3 +52,29 @@ def test_long_rows_keep_float4_loads():
     below, above = (gemm_us(1, 0, (1 << 23) + d, 64, 64, G.GNN_FLAG_F32_MFMA, reps=2)
                     for d in (-8, 8))
     assert above < 1.05 * below, (below, above)
+
+
+def test_second_k_segment_keeps_the_pipeline():
+    """Input gradient of a layer of h = 208 (a first K segment that ends inside
+    a stage of 32) against h = 224: 22 % dearer when all of the second segment
+    took the guarded loop."""
+    n, f = 8000, 256
+    dg = runtime.DeviceGraph(synth.identity_graph(n))
+    dg.prepare()
+    us = {}
+    for h in (208, 224):
+        w = np.full((f, h), 0.01, np.float32)
+        st = runtime.SageStack(dg, [synth.LayerParams(w, w)], f)
+        x, dy = torch.randn((n, f), device="cuda"), torch.randn((n, 2 * h), device="cuda")
+        us[h] = float("inf")
+        for _ in range(5):
+            st.forward(x)
+            G.gnn_timer_enable(True)
+            G.gnn_timer_reset()
+            for _ in range(20):
+                st.backward(dy)
+            torch.cuda.synchronize()
+            ms, launches, _ = G.gnn_timer_read("gemm_nt")
+            G.gnn_timer_enable(False)
+            us[h] = min(us[h], ms / launches * 1e3)
+    assert us[208] < 1.15 * us[224], us
