@@ -57,6 +57,8 @@ struct LayerLayout {
   // words each, K = h, N = f_in), written by the forward's weight split, at
   // off_sp and off_sp + sp_stride
   size_t sp_words, off_sp, sp_stride, saved_total;
+  // whether the forward product and the input gradient take those pieces
+  bool fwd_planes, dx_planes;
 };
 
 int resolve_order(const gnn_layer* L) {
@@ -168,10 +170,6 @@ GemmBatch dx_batch(int order, int32_t n, int32_t f_in, int32_t h,
   return b;
 }
 
-// Split products: W_self and W_neigh pre-split into their bf16 pieces in
-// the workspace (once per call, in the orientation of this batch's B), and
-// the batch's segments pointed at them: segment B pointers equal to W_self
-// take the first, W_neigh the second.
 // Points the batch's weight segments at bf16 pieces: p_self for W_self's,
 // p_neigh for W_neigh's, pw words per plane.
 void use_weight_planes(GemmBatch& b, const float* Ws, const uint32_t* p_self,
@@ -197,32 +195,29 @@ const uint32_t* saved_plane(const LayerLayout& o, const void* saved, int i) {
 // Forward product (split products): W_self and W_neigh split once into the
 // workspace in the forward orientation (op(B) = W, K = f_in, N = h) and, in
 // the same launch, into the saved buffer in the input gradient's (op(B) =
-// W^T, K = h, N = f_in), which gnn_prop_bwd reads instead of splitting.
+// W^T, K = h, N = f_in), which gnn_prop_bwd reads instead of splitting; each
+// where its product takes pieces.
 hipError_t attach_weight_planes(GemmBatch& b, const LayerLayout& o, char* ws, void* saved,
                                 const float* Ws, const float* Wn, int32_t f_in,
                                 int32_t h, hipStream_t s) {
-  if (b.mode != GEMM_SPLIT) return hipSuccess;
   uint32_t* wp[2] = {reinterpret_cast<uint32_t*>(ws + o.off_wp),
                      reinterpret_cast<uint32_t*>(ws + o.off_wp + round_up(o.wp_words * 4, 256))};
-  const SplitJob jobs[4] = {{Ws, h, f_in, h, 0, wp[0]},
-                            {Wn, h, f_in, h, 0, wp[1]},
-                            {Ws, h, h, f_in, 1, saved_plane(o, saved, 0)},
-                            {Wn, h, h, f_in, 1, saved_plane(o, saved, 1)}};
-  hipError_t e = split_b_planes_launch(jobs, 4, s);
-  if (e != hipSuccess) return e;
-  use_weight_planes(b, Ws, wp[0], wp[1], (int64_t)(b_planes_words(f_in, h) / 3));
-  return hipSuccess;
+  SplitJob jobs[4];
+  int nj = 0;
+  if (o.fwd_planes) {
+    jobs[nj++] = {Ws, h, f_in, h, 0, wp[0]};
+    jobs[nj++] = {Wn, h, f_in, h, 0, wp[1]};
+    use_weight_planes(b, Ws, wp[0], wp[1], (int64_t)(b_planes_words(f_in, h) / 3));
+  }
+  if (o.dx_planes) {
+    jobs[nj++] = {Ws, h, h, f_in, 1, saved_plane(o, saved, 0)};
+    jobs[nj++] = {Wn, h, h, f_in, 1, saved_plane(o, saved, 1)};
+  }
+  return nj ? split_b_planes_launch(jobs, nj, s) : hipSuccess;
 }
 
 GemmBatch with_mode(GemmBatch b, int32_t mode) {
   b.mode = mode;
-  return b;
-}
-// The forward product's or input gradient's batch: with split products its
-// weights come as planes.
-GemmBatch with_planes(GemmBatch b, int32_t mode) {
-  b.mode = mode;
-  b.b_planes = mode == GEMM_SPLIT;
   return b;
 }
 
@@ -248,9 +243,11 @@ LayerLayout layer_layout(const gnn_csr* csr, const gnn_layer* L) {
   }
   const int32_t bf = gemm_mode(L->flags);
   const size_t gemm_w = gemm_workspace_bytes(with_mode(dw_batch(o.order, n, f_in, h, 0, f_in, 0, 0, 0, 2 * h, 0, 2 * h, 0, 0), bf));
-  const size_t gemm = std::max(
-      gemm_workspace_bytes(with_planes(fwd_batch(o.order, n, f_in, h, 0, f_in, 0, 0, 0, 0, 0, 0, 0, 2 * h, 0, 0), bf)),
-      gemm_workspace_bytes(with_planes(dx_batch(o.order, n, f_in, h, 0, 2 * h, 0, 2 * h, 0, 0, 0, f_in, 0, f_in), bf)));
+  const GemmBatch fwd = gemm_with_planes(with_mode(fwd_batch(o.order, n, f_in, h, 0, f_in, 0, 0, 0, 0, 0, 0, 0, 2 * h, 0, 0), bf), true);
+  const GemmBatch dx = gemm_with_planes(with_mode(dx_batch(o.order, n, f_in, h, 0, 2 * h, 0, 2 * h, 0, 0, 0, f_in, 0, f_in), bf), true);
+  const size_t gemm = std::max(gemm_workspace_bytes(fwd), gemm_workspace_bytes(dx));
+  o.fwd_planes = fwd.b_planes;
+  o.dx_planes = dx.b_planes;
   // split products: W_self and W_neigh as bf16 pieces in the forward
   // product's orientation (K = f_in, N = h) in the workspace; the input
   // gradient's (K = h, N = f_in) in the saved buffer
@@ -448,15 +445,17 @@ size_t gnn_gemm_workspace_bytes(int32_t M, int32_t N, int32_t K) {
   b.p[0].M = M;
   b.p[0].N = N;
   b.p[0].seg[0].K = K;
-  // the largest need of the three product modes (their work splits differ)
+  // the largest need of the three product modes and of both kernels for split
+  // products (their work splits differ; which one runs depends on trans_a too)
   size_t need = 0;
   for (const int32_t mode : {GEMM_SPLIT, GEMM_BF16, GEMM_F32}) {
     b.mode = mode;
-    b.b_planes = gemm_use_planes(M, mode);
     need = std::max(need, gemm_workspace_bytes(b));
   }
-  const size_t part = round_up(need, 256);
-  return part + (gemm_use_planes(M, GEMM_SPLIT) ? round_up(b_planes_words(K, N) * 4, 256) : 0);
+  b.mode = GEMM_SPLIT;
+  b.b_planes = K > 0 && M >= GEMM_PLANES_ROWS;
+  if (b.b_planes) need = std::max(need, gemm_workspace_bytes(b));
+  return round_up(need, 256) + (b.b_planes ? round_up(b_planes_words(K, N) * 4, 256) : 0);
 }
 
 gnn_status gnn_gemm(int32_t trans_a, int32_t trans_b, int32_t M, int32_t N,
@@ -487,8 +486,8 @@ gnn_status gnn_gemm(int32_t trans_a, int32_t trans_b, int32_t M, int32_t N,
   b.p[0].C = C;
   b.p[0].ldc = ldc;
   // B split into its pieces once (workspace, after the partial tiles)
-  const bool presplit = K > 0 && gemm_use_planes(M, b.mode);
-  b.b_planes = presplit;
+  b = gemm_with_planes(b);
+  const bool presplit = b.b_planes;
   const size_t part = round_up(gemm_workspace_bytes(b), 256);
   const size_t need = part + (presplit ? round_up(b_planes_words(K, N) * 4, 256) : 0);
   if (workspace_bytes < need || (need > 0 && !workspace))
@@ -693,7 +692,7 @@ gnn_status gnn_prop_bwd(const gnn_csr* csr, const gnn_layer* layer,
       bx.mode = bf;
       bx.p[0].mask = dx_mask;
       bx.p[0].ld_mask = layer->ld_x;
-      if (bx.mode == GEMM_SPLIT && saved) {  // the pieces the forward call saved
+      if (o.dx_planes && saved) {  // the pieces the forward call saved
         // (saved is NULL only for n = 0, where the product has no tiles)
         use_weight_planes(bx, W_self, saved_plane(o, saved, 0), saved_plane(o, saved, 1),
                           (int64_t)(b_planes_words(h, f_in) / 3));
@@ -724,7 +723,7 @@ gnn_status gnn_prop_bwd(const gnn_csr* csr, const gnn_layer* layer,
       GemmBatch bx = dx_batch(1, n, f_in, h, G, ld_g, G + h, ld_g, W_self,
                               W_neigh, dX, layer->ld_dx, V, o.ld_v);
       bx.mode = bf;
-      if (bx.mode == GEMM_SPLIT && saved) {  // the pieces the forward call saved
+      if (o.dx_planes && saved) {  // the pieces the forward call saved
         // (saved is NULL only for n = 0, where the product has no tiles)
         use_weight_planes(bx, W_self, saved_plane(o, saved, 0), saved_plane(o, saved, 1),
                           (int64_t)(b_planes_words(h, f_in) / 3));

@@ -1712,13 +1712,6 @@ hipError_t split_b_planes_launch(const SplitJob* jobs, int njobs, hipStream_t s)
   return hipGetLastError();
 }
 
-bool gemm_use_planes(int32_t M, int32_t mode) { return mode == GEMM_SPLIT && M >= 512; }
-
-GemmBatch gemm_with_planes(GemmBatch b) {
-  b.b_planes = gemm_use_planes(b.p[0].M, b.mode);
-  return b;
-}
-
 size_t gemm_planes_bytes(const GemmBatch* b, int n) {
   size_t bytes = 0;
   for (int i = 0; i < n; ++i)
@@ -1763,7 +1756,7 @@ struct Shape {
   int splits;
   int too_big;  // more tiles than the 32-bit tile numbers hold: no launch
   int bn;     // tile width (64, 96 or 128 with planes, else 128)
-  int chain;  // with planes: CHAIN
+  int chain;  // with planes: CHAIN (64 columns)
 };
 
 // K depth of a stage of the batch's kernel.
@@ -1771,10 +1764,12 @@ static int stage_k(const GemmBatch& b) {
   return b.mode == GEMM_BF16 ? BK16 : b.mode == GEMM_F32 ? BK : b.b_planes ? BKP : BKS;
 }
 
-static Shape gemm_shape(const GemmBatch& b) {
+// The work split of the general kernels (for a batch marked b_planes, the
+// one that the split kernel would take without them).
+static Shape general_shape(const GemmBatch& b) {
   Shape s;
   memset(&s, 0, sizeof(s));
-  const int BK = stage_k(b);
+  const int BK = b.mode == GEMM_BF16 ? BK16 : b.mode == GEMM_F32 ? gnnprop::BK : BKS;
   const int M = b.p[0].M;
   s.tiles_m = (int)ceil_div(M, BM);
   s.tiles_n0 = (int)ceil_div(b.p[0].N, BN);
@@ -1817,7 +1812,7 @@ static Shape gemm_shape(const GemmBatch& b) {
   const int slots = MAX_BLOCKS;
   const int64_t rounds = ceil_div(s.tiles, slots);
   const double fill = (double)s.tiles / (double)(rounds * slots);
-  const int kt32 = b.mode == GEMM_SPLIT && !b.b_planes ? (s.ktiles + 1) / 2 : s.ktiles;
+  const int kt32 = b.mode == GEMM_SPLIT ? (s.ktiles + 1) / 2 : s.ktiles;
   const int64_t iters32 = (int64_t)s.tiles * kt32;
   const bool one_per_cu = s.tiles >= slots * 7 / 16 &&
                           ((s.tiles <= slots / 2 && kt32 <= 40) ||
@@ -1833,62 +1828,147 @@ static Shape gemm_shape(const GemmBatch& b) {
     // sharing a tile are consecutive and each holds a partial of it
     s.nblocks = (int)std::min<int64_t>(slots, s.iters);
   }
-  if (b.b_planes) {
-    // Tiles of 64, 96 or 128 columns, whole (one block each, two per CU) or
-    // split along K: whichever the measured times of a launch put first.  A
-    // block with a CU-mate takes s2 us per 32-deep stage, one alone s1, and
-    // 8 us besides (launch, first loads, output); a split launch pays its
-    // reduction on top.  Measured (before: 128 columns only): 8000 x 604, K =
-    // 1024: 441 tiles of 96 columns 67 us, 315 of 128 80; 8000 x 256, K =
-    // 608: 252 tiles of 64 26 us, split along K 32 + 10; 20000 x 1024, K =
-    // 200: 1,256 whole tiles 75 us, stream-K 70 + 27.
-    // Where the rule above shares tiles and whole ones are faster, CHAIN
-    // keeps the result as accurate as the partial sums, however many tiles
-    // there are: stream-K over 512 blocks cuts up to 511 of them (relative
-    // error at 6600 x 1536, K = 600, 624 tiles: shared 3.2e-7, whole 3.7e-7,
-    // whole with CHAIN 9.6e-8; 20000 x 512, K = 400: 2.6e-7, 2.9e-7, 8.3e-8).
-    const double s1[3] = {0.98, 1.26, 1.5}, s2[3] = {1.4, 1.9, 2.5}, fixed = 8.0;
-    const bool shared = s.nblocks != s.tiles;
-    const bool chain = shared;
-    const int parts = s.splits;
-    auto per_stage = [&](int i, int blocks) { return blocks <= NUM_CU ? s1[i] : s2[i]; };
-    auto whole_stage = [&](int i, int blocks) {
-      return per_stage(i, blocks) * (chain && blocks > NUM_CU ? 1.2 : 1.0);
-    };
-    double best = 1e300;
-    if (shared) best = fixed + s2[2] * (double)s.iters / s.nblocks + 9.0 + 0.03 * s.nblocks;
-    Shape c = s;
-    for (int i = 2; i >= 0; --i) {
-      c.bn = 64 + 32 * i;
-      c.tiles_n0 = (int)ceil_div(b.p[0].N, c.bn);
-      c.tiles_n = c.tiles_n0 + (b.nprob > 1 ? (int)ceil_div(b.p[1].N, c.bn) : 0);
-      if ((int64_t)c.tiles_m * c.tiles_n > INT32_MAX) continue;
-      c.tiles = c.tiles_m * c.tiles_n;
-      c.iters = (int64_t)c.tiles * c.ktiles;
-      c.splits = 1;
-      c.nblocks = c.tiles;
-      c.chain = chain;
-      const int rem = c.tiles % slots;
-      const double t = (c.tiles / slots) * (fixed + whole_stage(i, slots) * c.ktiles) +
-                       (rem == 0 ? 0 : fixed + whole_stage(i, rem) * c.ktiles);
-      if (t < best && !(chain && c.bn == BN)) {  // (no registers for CHAIN at 128)
+  return s;
+}
+
+// Modelled time of a launch (us): `blocks` blocks, two per CU, of `stages`
+// K stages each, in rounds of one block per slot.  A block with a CU-mate
+// takes s2 us a stage, one alone s1, and `fixed` besides.
+static double rounds_us(int64_t blocks, double stages, double fixed, double s1, double s2) {
+  const int64_t rem = blocks % MAX_BLOCKS;
+  return (double)(blocks / MAX_BLOCKS) * (fixed + s2 * stages) +
+         (rem ? fixed + (rem > NUM_CU ? s2 : s1) * stages : 0.0);
+}
+
+static double batch_mb(const GemmBatch& b) {  // of the output
+  return 4e-6 * b.p[0].M * ((double)b.p[0].N + (b.nprob > 1 ? b.p[1].N : 0));
+}
+
+static bool batch_ragged(const GemmBatch& b, int bn) {  // tiles with columns past N
+  return b.p[0].N % bn || (b.nprob > 1 && b.p[1].N % bn);
+}
+
+static bool partial_stages(const GemmBatch& b, int k) {  // a K segment ends inside a stage
+  return b.p[0].seg[0].K % k || (b.p[0].nseg > 1 && b.p[0].seg[1].K % k);
+}
+
+// The work split of a batch whose B comes as planes, and its modelled time.
+//
+// Tiles of 64, 96 or 128 columns, each one block's or split along K over
+// several, whichever the model puts first.  `gen`, the split that the general
+// kernel would take, sets what the sums may be: where it has whole tiles, all
+// of K may be one chain of the matrix cores; where it shares them, a part may
+// be no deeper than gen's, or each stage is summed from zero (CHAIN), which
+// is more accurate than any partial sums (K = 602, relative error: one chain
+// 3.7e-7, 32 parts 1.2e-7, CHAIN 9.6e-8) and has registers only at 64
+// columns.  The constants are fitted to 9,300 timed launches (M = 512 to
+// 50,000, N = 8 to 1,024, K = 16 to 2,048; relative spread 6 %), the cost of
+// a reduction raised from 0.4 to 2.4 us, which it takes between the launches
+// of a layer.  Whole call in us, with the eight-wavefront kernel of 128-column
+// tiles that these launches had before / with the rule that knew CHAIN for
+// whole tiles only and no general kernel (below) / now: 1000 x 602, K = 1024:
+// 29 / 35 / 27; 4000 x 256, K = 1024: 33 / 40 / 32; 512 x 41, K = 256: 13 / 17 /
+// 11; 1000 x 256, K = 602: 26 / 29 / 16; 20000 x 1024, K = 602: 172 / 136 (with
+// the larger error of one chain) / 166.
+static Shape planes_shape(const GemmBatch& b, const Shape& gen, double* us) {
+  const double fixed[3] = {0.7, 2.3, 5.6}, s1[3] = {0.89, 1.1, 1.41}, s2[3] = {1.36, 1.59, 2.03};
+  const bool whole_ok = gen.nblocks == gen.tiles;
+  const int parts = gen.splits > 1 ? gen.splits : MAX_BLOCKS;  // stream-K: CHAIN only
+  Shape s = gen;
+  const bool tail = partial_stages(b, BKP);
+  s.ktiles = 0;
+  for (int i = 0; i < b.nprob; ++i) {
+    const GemmProblem& p = b.p[i];
+    s.kt0[i] = (int)ceil_div(p.seg[0].K, BKP);
+    s.ktiles = std::max(s.ktiles, s.kt0[i] + (p.nseg > 1 ? (int)ceil_div(p.seg[1].K, BKP) : 0));
+  }
+  s.ktiles = std::max(s.ktiles, 1);
+  double best = 1e300;
+  Shape c = s;
+  for (int i = 2; i >= 0; --i) {
+    c.bn = 64 + 32 * i;
+    c.tiles_n0 = (int)ceil_div(b.p[0].N, c.bn);
+    c.tiles_n = c.tiles_n0 + (b.nprob > 1 ? (int)ceil_div(b.p[1].N, c.bn) : 0);
+    const int64_t tiles = (int64_t)c.tiles_m * c.tiles_n;
+    if (tiles > INT32_MAX) continue;
+    c.tiles = (int)tiles;
+    c.iters = tiles * c.ktiles;
+    auto take = [&](int splits, int chain) {
+      const int64_t blocks = tiles * splits;
+      const double rounds = (double)ceil_div(blocks, (int64_t)MAX_BLOCKS);
+      double t = 5.8 + rounds * 0.34 * tail +
+                 rounds_us(blocks, (double)ceil_div(c.ktiles, splits), fixed[i],
+                           s1[i] + 0.05 * chain, s2[i] + 0.07 * chain);
+      if (splits > 1)
+        t += 2.4 + 0.51 * 4e-6 * BM * c.bn * (double)blocks;
+      else
+        t += 0.13 * batch_mb(b) + rounds * 0.57 * batch_ragged(b, c.bn);
+      if (t < best) {
         best = t;
         s = c;
+        s.splits = splits;
+        s.chain = chain;
+        s.nblocks = (int)blocks;
       }
-      c.splits = std::min(c.ktiles, slots / c.tiles);  // 0 for more tiles than slots
-      if (parts > 1 && c.splits >= parts) {  // as many parts as above: as accurate
-        c.nblocks = c.tiles * c.splits;
-        c.chain = 0;
-        const double ts = fixed + per_stage(i, c.nblocks) * (double)ceil_div(c.ktiles, c.splits) +
-                          9.0 + 0.03 * c.nblocks * c.bn / BN;
-        if (ts < best) {
-          best = ts;
-          s = c;
-        }
-      }
+    };
+    if (whole_ok) take(1, 0);
+    if (c.bn == 64 && !whole_ok) take(1, 1);
+    const int most = whole_ok ? 1 : (int)std::min<int64_t>(c.ktiles, MAX_BLOCKS / tiles);
+    for (int sp = 2; sp <= most; sp += std::max(1, sp / 2)) {
+      if (c.bn == 64) take(sp, 1);
+      if (sp >= std::min(parts, c.ktiles)) take(sp, 0);
     }
+    if (most > 1 && most >= std::min(parts, c.ktiles)) take(most, 0);
   }
+  *us = best;
   return s;
+}
+
+// The modelled time of the general split kernel's launch, fitted likewise
+// (relative spread 9 %).  It needs no launch that splits B, and its 128-column
+// tiles of eight wavefronts write wide outputs of few K stages faster: 50000 x
+// 1024, K = 16 50 us, with pieces 59; 8000 x 1024, K = 64: 18, 22; 4000 x
+// 1024, K = 400: 26, 31.
+static double general_us(const GemmBatch& b, const Shape& g) {
+  const double stages = g.splits > 1 ? (double)ceil_div(g.ktiles, g.splits)
+                                     : (double)g.iters / g.nblocks;
+  const bool whole = g.nblocks == g.tiles;
+  const double rounds = (double)ceil_div(g.nblocks, (int64_t)MAX_BLOCKS);
+  const double part_mb = 4e-6 * BM * BN;
+  const bool tail = partial_stages(b, BKS), ragged = whole && batch_ragged(b, BN);
+  if (b.trans_a)  // four wavefronts a block
+    return whole ? 7.3 + rounds_us(g.nblocks, stages, 0.0, 0.9, 1.2) +
+                       7.7 * (b.p[0].M % BM || batch_ragged(b, BN))
+                 : 7.3 + rounds * stages * (g.nblocks > NUM_CU ? 0.96 : 0.18) +
+                       0.41 * part_mb * g.nblocks;
+  return 7.5 + rounds_us(g.nblocks, stages, 0.0, 0.675, 1.31) +
+         rounds * (0.6 * tail + 2.2 * ragged) +
+         (whole ? 0.16 * batch_mb(b)
+                : g.splits > 1 ? 1.8 + 0.35 * part_mb * g.nblocks : 15.8 + 0.25 * part_mb * g.tiles);
+}
+
+static Shape gemm_shape(const GemmBatch& b) {
+  const Shape g = general_shape(b);
+  if (!b.b_planes || g.too_big || g.tiles == 0) return g;
+  double us;
+  return planes_shape(b, g, &us);
+}
+
+GemmBatch gemm_with_planes(GemmBatch b, bool ready) {
+  b.b_planes = 0;
+  if (b.mode != GEMM_SPLIT || (!ready && b.p[0].M < GEMM_PLANES_ROWS)) return b;
+  double split_us = ready ? 0.0 : 2.0;
+  for (int i = 0; i < b.nprob; ++i)
+    for (int k = 0; k < b.p[i].nseg; ++k) {
+      if (b.p[i].seg[k].K <= 0) return b;
+      if (!ready) split_us += 3e-6 * b.p[i].seg[k].K * (double)b.p[i].N;
+    }
+  const Shape g = general_shape(b);
+  if (g.too_big || g.tiles == 0) return b;
+  double us;
+  planes_shape(b, g, &us);
+  b.b_planes = us + split_us < general_us(b, g);
+  return b;
 }
 
 static bool batch_ok(const GemmBatch& b) {
@@ -2038,25 +2118,21 @@ hipError_t gemm_launch(const GemmBatch& b, void* workspace, size_t ws_bytes,
     else
       gemm_f32_kernel<true, true><<<grid, 256, 0, s>>>(g, fx);
   } else if (b.b_planes) {
-    auto width = [&](auto at, auto chain) {
-      constexpr bool AT = decltype(at)::value, CH = decltype(chain)::value;
-      if (sh.bn == 64)
-        gemm_planes_kernel<AT, 2, CH><<<grid, 256, 0, s>>>(g, fx);
+    auto width = [&](auto at) {
+      constexpr bool AT = decltype(at)::value;
+      if (sh.chain)
+        gemm_planes_kernel<AT, 2, true><<<grid, 256, 0, s>>>(g, fx);
+      else if (sh.bn == 64)
+        gemm_planes_kernel<AT, 2, false><<<grid, 256, 0, s>>>(g, fx);
       else if (sh.bn == 96)
-        gemm_planes_kernel<AT, 3, CH><<<grid, 256, 0, s>>>(g, fx);
-      else if constexpr (!CH)
+        gemm_planes_kernel<AT, 3, false><<<grid, 256, 0, s>>>(g, fx);
+      else
         gemm_planes_kernel<AT, 4, false><<<grid, 256, 0, s>>>(g, fx);
     };
-    auto trans = [&](auto chain) {
-      if (b.trans_a)
-        width(std::true_type{}, chain);
-      else
-        width(std::false_type{}, chain);
-    };
-    if (sh.chain)
-      trans(std::true_type{});
+    if (b.trans_a)
+      width(std::true_type{});
     else
-      trans(std::false_type{});
+      width(std::false_type{});
   } else if (!b.trans_a && !b.trans_b) {
     gemm_split_kernel<false, false, 8><<<grid, 512, 0, s>>>(g, fx);
   } else if (b.trans_a && !b.trans_b) {

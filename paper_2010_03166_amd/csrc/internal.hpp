@@ -191,13 +191,13 @@ struct SplitJob {
 constexpr int MAX_SPLIT_JOBS = 4;
 // Up to MAX_SPLIT_JOBS matrices split in one launch.
 hipError_t split_b_planes_launch(const SplitJob* jobs, int njobs, hipStream_t s);
-// Whether a product of M rows takes its B operand as planes: split products
-// of at least four row tiles of 128, each of which would otherwise split the
-// same values again.
-bool gemm_use_planes(int32_t M, int32_t mode);
-// The batch with b_planes set by that rule (its workspace size and launch
-// depend on it).
-GemmBatch gemm_with_planes(GemmBatch b);
+// The batch with b_planes set where the kernel that takes B as planes is the
+// faster one by the modelled times (gemm.hip).  `ready`: the planes are there
+// anyway; otherwise the launch that splits B counts, and only products of at
+// least GEMM_PLANES_ROWS rows (four row tiles of 128, each of which would otherwise split
+// the same values again) take planes.  Workspace size and launch depend on b_planes.
+constexpr int32_t GEMM_PLANES_ROWS = 512;
+GemmBatch gemm_with_planes(GemmBatch b, bool ready = false);
 // Bytes of the planes of every B operand of n batches marked b_planes, and
 // their splitting (one launch per MAX_SPLIT_JOBS operands), which points the
 // batches at them.

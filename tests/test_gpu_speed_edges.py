@@ -78,3 +78,17 @@ def test_second_k_segment_keeps_the_pipeline():
             G.gnn_timer_enable(False)
             us[h] = min(us[h], ms / launches * 1e3)
     assert us[208] < 1.15 * us[224], us
+
+
+@pytest.mark.parametrize("shape,other,limit", [
+    # one K range after the other on few CUs, or 16 parts of one stage and
+    # their reduction: 1.37 times the time of a K more than twice as deep, now 0.9
+    ((512, 41, 256), (512, 41, 602), 1.1),
+    # 32 and 42 parts of one or two stages: 2.4 times the shallow product's
+    # time, now 1.4
+    ((1000, 256, 602), (1000, 256, 64), 1.9),
+    ((700, 200, 1024), (700, 200, 41), 1.9),
+])
+def test_few_tiles_over_a_long_k(shape, other, limit):
+    a, b = gemm_us(0, 0, *shape), gemm_us(0, 0, *other)
+    assert a < limit * b, (a, b)
