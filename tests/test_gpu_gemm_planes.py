@@ -107,3 +107,76 @@ def test_two_segment_input_gradient(n, f, h):
     err = (dX.cpu().double() - g @ w.T).abs()
     bound = (24 * -(-h // 32) + 8) * 2.0 ** -23 * (g.abs() @ w.abs().T)
     assert (err <= bound).all(), float((err / bound).max())
+
+
+# every way the work split takes a product of 512 rows and more
+WAYS = [
+    (512, 64, 64),      # whole tiles of 64 columns, one chain over K
+    (50000, 96, 41),    # of 96
+    (8000, 1024, 602),  # of 128
+    (1000, 602, 128),   # 64 columns in place of parts: every stage from zero
+    (2000, 1200, 200),  # in place of stream-K
+    (1000, 256, 602),   # K over several blocks, every stage from zero
+    (6000, 301, 1500),  # the same in place of stream-K
+    (512, 64, 602),     # K over several blocks, 64 columns
+    (8000, 129, 1024),  # 96
+    (5000, 301, 4096),  # 128
+    (512, 41, 256),     # the kernel that splits both operands itself: parts
+    (8000, 512, 200),   # whole tiles
+    (50000, 512, 1024),  # stream-K
+]
+
+
+def _padded(x, ta):
+    x = x.T if ta else x
+    buf = torch.full((x.shape[0], -(-x.shape[1] // 4) * 4), float("nan"), device="cuda")
+    buf[:, : x.shape[1]] = x
+    return buf
+
+
+def _product(a, b, ta, tb):
+    M, K = a.shape
+    N = b.shape[1]
+    A, B = _padded(a, ta), _padded(b, tb)
+    C = torch.full((M, N), float("nan"), device="cuda")
+    ws = torch.empty(max(G.gnn_gemm_workspace_bytes(M, N, K), 256), dtype=torch.uint8,
+                     device="cuda")
+    G.gnn_gemm(ta, tb, M, N, K, A, A.stride(0), B, B.stride(0), C, N, 0, ws)
+    return C
+
+
+@pytest.mark.parametrize("M,N,K", WAYS)
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
+def test_every_way_of_splitting_the_work(M, N, K, ta, tb):
+    gen = torch.Generator(device="cuda").manual_seed(M + 3 * N + 7 * K)
+    a = torch.randn((M, K), device="cuda", generator=gen)
+    b = torch.randn((K, N), device="cuda", generator=gen)
+    err = (_product(a, b, ta, tb).double() - a.double() @ b.double()).abs()
+    bound = (12 * -(-K // 32) + 8) * 2.0 ** -23 * (a.double().abs() @ b.double().abs())
+    assert (err <= bound).all(), float((err / bound).max())
+
+
+@pytest.mark.parametrize("M,N,K", WAYS)
+@pytest.mark.parametrize("ta", [0, 1])
+@pytest.mark.parametrize("dense", ["a", "b"])
+def test_every_operand_bit_counts(M, N, K, ta, dense):
+    """One operand holds numbers of 24 significand bits (1 + 2^-9 + 2^-18 +
+    2^-23 times powers of two: three pieces, none 0), the other picks one of
+    them per output with a power of two: each result is exact in fp32, and a
+    product of pieces left out or doubled shows in every element."""
+    rng = np.random.default_rng(M + N + K)
+    sig = 1.0 + 2.0 ** -9 + 2.0 ** -18 + 2.0 ** -23
+    full = lambda r, c: (sig * rng.choice([1.0, -1.0], size=(r, c))
+                         * np.ldexp(1.0, rng.integers(-3, 4, size=(r, c)))).astype(np.float32)
+    if dense == "a":
+        a, b = full(M, K), np.zeros((K, N), np.float32)
+        k, w = rng.integers(0, K, N), np.ldexp(1.0, -rng.integers(0, 3, N)).astype(np.float32)
+        b[k, np.arange(N)] = w
+        want = a[:, k] * w
+    else:
+        a, b = np.zeros((M, K), np.float32), full(K, N)
+        k, w = rng.integers(0, K, M), np.ldexp(1.0, -rng.integers(0, 3, M)).astype(np.float32)
+        a[np.arange(M), k] = w
+        want = b[k] * w[:, None]
+    got = _product(torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda(), ta, 0)
+    assert torch.equal(got, torch.from_numpy(want).cuda())
