@@ -16,10 +16,9 @@
 // span all of them) is finished through LDS by the group holding its first
 // entry, adding the other groups' parts in group order.  One kernel, no
 // atomics, bit-reproducible, and work is balanced by entries, not rows.
-// Outputs are cut into up to 8 column slices, each
-// XCD gathering from one of them (the GPU form of the feature partition of
-// Section 5.3, Theorem 2 / Algorithm 7, with each XCD's L2 as the cache a
-// slice should fit).
+// Outputs are cut into column slices, most XCDs gathering from one of them
+// only (the GPU form of the feature partition of Section 5.3, Theorem 2 /
+// Algorithm 7, with each XCD's L2 as the cache a slice should fit).
 #include "internal.hpp"
 
 namespace gnnprop {
@@ -361,7 +360,9 @@ struct SpmmArgs {
   int64_t ld_res;
   const float* mask;
   int64_t ld_mask;
-  int32_t nslices;  // column slices: 1, 2, 4 or 8
+  int32_t nslices;  // column slices, none empty
+  int32_t share;    // XCDs of a slice of its own (0 for more than 8 slices)
+  int32_t per;      // blocks per XCD
   int32_t sw;       // slice width in columns
   int32_t nwin;     // workgroups per slice: plan windows / wpb, rounded up
   int32_t wpb;      // consecutive plan windows per workgroup (1 or 2)
@@ -369,11 +370,10 @@ struct SpmmArgs {
   int32_t weights;  // SpmmWeights
 };
 
-// Column slices.  Blocks are dispatched round-robin over the 8 XCDs, so with
-// S slices (a power of two up to 8) block b works on slice b mod S of window
-// (group) b / S: an XCD gathers from one n x sw slice only, which its L2
-// holds or half holds (the cache-sized feature partitions of Theorem 2 /
-// Algorithm 7).  See spmm_args for S.
+// Column slices.  Blocks are dispatched round-robin over the 8 XCDs, so block
+// b runs on XCD b mod 8, which should gather from one n x sw slice only that
+// its L2 holds or half holds (the cache-sized feature partitions of Theorem 2 /
+// Algorithm 7).  See spmm_args for the slices.
 //
 // A group of G lanes covers G * W consecutive columns of the slice per pass
 // (W = 4: float4 per lane, so one gathered 256-byte row segment of a
@@ -383,6 +383,30 @@ struct SpmmArgs {
 // prefetched), walked with lane shuffles, D neighbour rows in flight.  EPI
 // is the epilogue; OFF32 marks inputs below 4 GiB, whose gather offsets fit
 // 32 bits.
+// The slice and window (group) of this block.  Every XCD takes `per` blocks.
+// With up to 8 slices each has `share` XCDs to itself, which walk its first
+// windows; what the XCDs left over (8 mod slices) take are the last windows of
+// all slices, slice after slice.  Every XCD so does an eighth of the work and
+// a slice's first windows, hub rows among them or not, start at once.  (Blocks
+// b mod 8 on slices 0 to 7, the last ones empty, left their XCDs idle: 50,000 x
+// 160, 5 slices of 32: 152 -> 104 us; 20,000 x 200, 7 slices: 57 -> 51.)  With
+// more slices than XCDs every XCD takes an eighth of them all, in order.
+__device__ inline bool slice_of(const SpmmArgs& a, int& slice, int& win) {
+  const int x = blockIdx.x & 7, q = blockIdx.x >> 3;
+  const int own = a.share * a.nslices;
+  if (x < own) {
+    slice = x % a.nslices;
+    win = q * a.share + x / a.nslices;
+  } else {
+    const int first = a.share * a.per, rem = a.nwin - first;
+    if (rem <= 0) return false;
+    const uint32_t l = (uint32_t)(x - own) * (uint32_t)a.per + (uint32_t)q;
+    slice = (int)(l / (uint32_t)rem);
+    win = first + (int)(l % (uint32_t)rem);
+  }
+  return slice < a.nslices && win < a.nwin;
+}
+
 template <bool VEC>
 struct Vec;
 template <>
@@ -506,8 +530,8 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs a) {
   __shared__ int head_row[256], tail_row[256], starts[256];
   auto gtid = [&](int g) { return (g / gpw) * 64 + (g % gpw) * G; };
 
-  const int slice = blockIdx.x & (a.nslices - 1);
-  const int win = blockIdx.x / a.nslices;
+  int slice, win;
+  if (!slice_of(a, slice, win)) return;
   // Consecutive windows own consecutive rows and entries (an empty window
   // inside a hub row starts and ends where the next row starts), so
   // windows k .. k + wpb - 1 together are one run of whole rows.
@@ -721,8 +745,8 @@ __global__ __launch_bounds__(256) void spmm_floor_kernel(SpmmArgs a) {
   __shared__ T part[256];
   auto gtid = [&](int g) { return (g / gpw) * 64 + (g % gpw) * G; };
 
-  const int slice = blockIdx.x & (a.nslices - 1);
-  const int win = blockIdx.x / a.nslices;
+  int slice, win;
+  if (!slice_of(a, slice, win)) return;
   const int k0 = win * a.wpb, k1 = min(k0 + a.wpb, a.nblk) - 1;
   const int4 bi0 = a.binfo[k0], bi1 = a.binfo[k1];
   const int r_lo = bi0.x, r_hi = bi1.y, B = bi0.z, E = bi1.w;
@@ -821,7 +845,7 @@ static double spmm_bytes(int32_t n, int64_t nnz, int32_t w, int out_bytes = 4) {
 
 template <int G, bool VEC, int EPI, bool RAG>
 static void spmm_go(const SpmmArgs& a, bool off32, hipStream_t s) {
-  const unsigned grid = (unsigned)((int64_t)a.nwin * a.nslices);
+  const unsigned grid = 8u * (unsigned)a.per;
   if (off32)
     spmm_kernel<G, SPMM_DEPTH, VEC, EPI, true, RAG><<<grid, 256, 0, s>>>(a);
   else
@@ -924,6 +948,7 @@ static SpmmArgs spmm_args(const SpmmCall& c, bool* vec_out, bool* off32_out) {
     a.nslices = c.w >= 32 ? 8 : 1;
     a.sw = (int32_t)round_up(ceil_div(c.w, a.nslices), 4);
   }
+  a.nslices = (int32_t)ceil_div(c.w, a.sw);
   // Two windows per workgroup once the grid would pass 16,384 workgroups:
   // each workgroup pays a chain of dependent loads (window record, entry
   // metadata, first gathers) before its gathers stream, which a longer entry
@@ -932,6 +957,8 @@ static SpmmArgs spmm_args(const SpmmCall& c, bool* vec_out, bool* off32_out) {
   a.nblk = (int32_t)d.nblk;
   a.wpb = d.nblk * a.nslices > 16384 ? 2 : 1;
   a.nwin = (int32_t)ceil_div(d.nblk, (int64_t)a.wpb);
+  a.share = 8 / a.nslices;
+  a.per = (int32_t)ceil_div((int64_t)a.nwin * a.nslices, 8);
   // Gather offsets in 32 bits when the input spans less than 4 GiB.
   const bool off32 = ((int64_t)(c.n - 1) * c.ld_in + c.w) * 4 < (int64_t(1) << 32);
   *vec_out = vec;
@@ -957,7 +984,7 @@ hipError_t spmm_launch(const SpmmCall& c, hipStream_t s) {
 
 template <int G, bool RAG>
 static void spmm_floor_go(const SpmmArgs& a, bool off32, hipStream_t s) {
-  const unsigned grid = (unsigned)((int64_t)a.nwin * a.nslices);
+  const unsigned grid = 8u * (unsigned)a.per;
   if (off32)
     spmm_floor_kernel<G, SPMM_DEPTH, true, RAG><<<grid, 256, 0, s>>>(a);
   else
