@@ -916,7 +916,7 @@ static SpmmArgs spmm_args(const SpmmCall& c, bool* vec_out, bool* off32_out) {
   a.ld_mask = c.ld_mask;
   a.weights = c.weights;
   // float4 lanes whenever rows start 16-byte aligned (the ragged end of a
-  // width that is not a multiple of 4 is read and written per component)
+  // width that is not a multiple of 4 is written per component)
   const bool out_ok = c.epilogue == SPMM_STORE_BF16
                           ? (reinterpret_cast<uintptr_t>(c.out) % 8 == 0 && c.ld_out % 4 == 0)
                           : vec4_ok(c.out, c.ld_out);
@@ -934,15 +934,21 @@ static SpmmArgs spmm_args(const SpmmCall& c, bool* vec_out, bool* off32_out) {
   // (214), 20,000 x 200 189 / 106 / 73 (84), 20,000 x 512 378 / 199 / 113
   // (114), 50,000 x 340 934 / 481 / 285 (385).  Graphs whose largest row is
   // short would take fewer (20,000 x 200 at most 1,000 entries a row: 39 in
-  // two), but the degrees are not known here.  Small graphs take twice as many
-  // while their workgroups would leave the chip short of them.  Slices are a
-  // multiple of 16 columns wide, so that they start on 64 bytes wherever rows
-  // do and a gathered slice row touches no line more than it fills (8,000 x
-  // 602: eight of 80 columns 27.7 us, sixteen of 40 41.1).  Rows off 16-byte
-  // alignment (float lanes) keep eight slices.
+  // two), but the degrees are not known here: 8,000 x 72 to 128 without a cap
+  // pay up to 10 % (x 128: 22 -> 24) for what capped graphs gain (22 -> 12).
+  // Up to 1,500 workgroups a launch takes twice as many slices, down to 16
+  // columns from 300 windows on (8,000 x 64 without a cap: 22 us in 16
+  // columns, 24 in 32).  Below, 32 are better throughout (1,000 x 64: 10 us, in
+  // 16 columns 15; 3,000 x 64 11, 15), and so is one slice up to 31 columns
+  // (1,000 x 24: 10, 15; 8,000 x 24 12, 16).  Slices are a multiple of 16
+  // columns wide and so start on 64 bytes wherever rows do (8,000 x 602: eight
+  // of 80 columns 27.7 us, sixteen of 40 41.1).  Rows off 16-byte alignment
+  // (float lanes) keep eight slices.
   if (vec) {
     a.nslices = c.w <= 32 ? 1 : c.w <= 64 ? 2 : c.w <= 128 ? 4 : 8;
-    while (a.nslices < 8 && d.nblk * a.nslices < 1500 && c.w > 16 * a.nslices) a.nslices *= 2;
+    const int least = d.nblk < 300 ? 32 : 16;
+    while (c.w >= 32 && a.nslices < 8 && d.nblk * a.nslices < 1500 && c.w > least * a.nslices)
+      a.nslices *= 2;
     a.sw = (int32_t)round_up(ceil_div(c.w, a.nslices), 16);
   } else {
     a.nslices = c.w >= 32 ? 8 : 1;

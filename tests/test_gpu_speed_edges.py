@@ -113,3 +113,11 @@ def test_slices_leave_no_xcd_idle():
     g = _capped_graph(50000, 40.0, 1000)
     a, b = spmm_us(g, 160, 160), spmm_us(g, 256, 256)
     assert a < 0.72 * b, (a, b)
+
+
+def test_narrow_slices_not_on_small_graphs():
+    """24 columns of a 1,000-node graph: 1.4 times the time of 144 columns in
+    slices of 16 columns, as long in one slice."""
+    g = _capped_graph(1000, 10.0, 999)
+    a, b = spmm_us(g, 24, 32), spmm_us(g, 144, 144)
+    assert a < 1.2 * b, (a, b)
