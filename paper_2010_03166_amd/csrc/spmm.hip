@@ -943,7 +943,12 @@ static SpmmArgs spmm_args(const SpmmCall& c, bool* vec_out, bool* off32_out) {
   // (1,000 x 24: 10, 15; 8,000 x 24 12, 16).  Slices are a multiple of 16
   // columns wide and so start on 64 bytes wherever rows do (8,000 x 602: eight
   // of 80 columns 27.7 us, sixteen of 40 41.1).  Rows off 16-byte alignment
-  // (float lanes) keep eight slices.
+  // (float lanes) take eight slices up to 512 columns; beyond, eight would be
+  // wider than the 64 lanes of a group and walk the entries twice or more:
+  // slices of 32 columns up to 640 and of 64 from there, 32 at most (1,000 x
+  // 602: 12 us, eight of 76 31, sixteen of 40 18; 20,000 x 602 208, 333, 322;
+  // 20,000 x 1026: 346 in slices of 64, 502, 637), unless so many workgroups
+  // would pass the largest grid.
   if (vec) {
     a.nslices = c.w <= 32 ? 1 : c.w <= 64 ? 2 : c.w <= 128 ? 4 : 8;
     const int least = d.nblk < 300 ? 32 : 16;
@@ -953,6 +958,8 @@ static SpmmArgs spmm_args(const SpmmCall& c, bool* vec_out, bool* off32_out) {
   } else {
     a.nslices = c.w >= 32 ? 8 : 1;
     a.sw = (int32_t)round_up(ceil_div(c.w, a.nslices), 4);
+    if (c.w > 512 && d.nblk < (1 << 18))
+      a.sw = c.w <= 640 ? 32 : (int32_t)round_up(ceil_div(c.w, 32), 64);
   }
   a.nslices = (int32_t)ceil_div(c.w, a.sw);
   // Two windows per workgroup once the grid would pass 16,384 workgroups:

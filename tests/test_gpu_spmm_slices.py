@@ -54,3 +54,19 @@ def test_two_windows_per_workgroup_many_slices():
     assert -(-LARGE.nnz // 256) * 8 > 16384
     test_spmm_slices("large", 604, 0)
     test_spmm_slices("large", 640, 1)
+
+
+@pytest.mark.parametrize("w", [31, 33, 257, 511, 513, 639, 641, 1025, 2049, 2113])
+@pytest.mark.parametrize("transpose", [0, 1])
+def test_float_lanes(w, transpose):
+    """Rows off 16-byte alignment: eight slices, slices of 32 and 64 columns
+    (more of them than XCDs), and wider ones."""
+    dg = runtime.DeviceGraph(SMALL)
+    dg.prepare()
+    x = np.random.default_rng(w + transpose).standard_normal((SMALL.n, w)).astype(np.float32)
+    xin, out = _exact_rows(SMALL.n, w, w, x), _exact_rows(SMALL.n, w, w)
+    G.gnn_spmm(dg.struct(), transpose, w, xin, w, out, w, None)
+    torch.cuda.synchronize()
+    ref = O.spmm_transpose(SMALL, x) if transpose else O.spmm(SMALL, x)
+    got = out.cpu().numpy().astype(np.float64)
+    assert np.abs(got - ref).max() <= TOL * np.abs(ref).max()
