@@ -266,8 +266,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // consecutive columns per thread of a 256-thread block.  Run by
 // gemm_fixup_kernel, or by extra blocks at the end of the next GEMM launch
 // on the stream (which reads the partials the earlier launch wrote).
-__host__ __device__ inline int fix_chunks(int bn) { return BM * bn / 1024; }
+__host__ __device__ constexpr int fix_chunks(int bn) { return BM * bn / 1024; }
 
+template <int BNT>
 __device__ inline void fixup_chunk(const GemmKArgs& g, int t, int chunk) {
   const int64_t first = (int64_t)t * g.ktiles, last = first + g.ktiles - 1;
   int b0 = 0, b1 = 0;
@@ -276,13 +277,11 @@ __device__ inline void fixup_chunk(const GemmKArgs& g, int t, int chunk) {
     b1 = block_of(last, g.iters, g.nblocks);
     if (b0 == b1) return;  // written directly by its only block
   }
-  const TileInfo ti = tile_info(g, t, g.bn);
+  const TileInfo ti = tile_info(g, t, BNT);
   const GemmProblem& P = ti.pi ? g.p[1] : g.p[0];
   const int e = chunk * 1024 + threadIdx.x * 4;
-  // (64, 96 or 128: a run-time division costs 0.5 us of a small reduction)
-  const int rl = g.bn == BN ? e / BN : g.bn == 64 ? e / 64 : e / 96;
-  const int cl = e - rl * g.bn;
-  const int64_t tile = (int64_t)BM * g.bn;
+  const int rl = e / BNT, cl = e % BNT;
+  constexpr int64_t tile = BM * BNT;
   const int row = ti.m0 + rl, col = ti.n0 + cl;
   if (row >= g.M || col >= P.N || row < ti.r0) return;
   float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -334,8 +333,9 @@ __device__ inline void fixup_chunk(const GemmKArgs& g, int t, int chunk) {
   }
 }
 
+template <int BNT>
 __global__ __launch_bounds__(256) void gemm_fixup_kernel(GemmKArgs g) {
-  fixup_chunk(g, blockIdx.x, blockIdx.y);
+  fixup_chunk<BNT>(g, blockIdx.x, blockIdx.y);
 }
 
 // Blocks past the GEMM's own run the chunks of a reduction left by the
@@ -344,8 +344,8 @@ __device__ inline bool run_pending_fixup(const GemmKArgs& g, const GemmKArgs& fx
   if ((int)blockIdx.x < g.nblocks) return false;
   if (threadIdx.x >= 256) return true;  // a chunk takes 256 threads
   const int f = (int)blockIdx.x - g.nblocks;
-  const int chunks = fix_chunks(fx.bn);
-  fixup_chunk(fx, f / chunks, f % chunks);
+  constexpr int chunks = fix_chunks(BN);  // (only tiles of BN columns are held)
+  fixup_chunk<BN>(fx, f / chunks, f % chunks);
   return true;
 }
 
@@ -1967,7 +1967,9 @@ GemmBatch gemm_with_planes(GemmBatch b, bool ready) {
   if (g.too_big || g.tiles == 0) return b;
   double us;
   planes_shape(b, g, &us);
-  b.b_planes = us + split_us < general_us(b, g);
+  // (in a layer, whose operands are not in the caches, the general kernel has
+  // been up to 4 % dearer than the model says: 8000 x 512, K = 602)
+  b.b_planes = us + split_us < 1.04 * general_us(b, g);
   return b;
 }
 
@@ -2004,7 +2006,13 @@ double gemm_flops(const GemmBatch& b) {
 // The reduction of a launch's shared tiles as its own kernel.
 static hipError_t fixup_launch(const GemmKArgs& g, hipStream_t s) {
   timer_begin(GNN_K_GEMM_REDUCE, s);
-  gemm_fixup_kernel<<<dim3((unsigned)g.tiles, (unsigned)fix_chunks(g.bn)), 256, 0, s>>>(g);
+  const dim3 grid((unsigned)g.tiles, (unsigned)fix_chunks(g.bn));
+  if (g.bn == 64)
+    gemm_fixup_kernel<64><<<grid, 256, 0, s>>>(g);
+  else if (g.bn == 96)
+    gemm_fixup_kernel<96><<<grid, 256, 0, s>>>(g);
+  else
+    gemm_fixup_kernel<BN><<<grid, 256, 0, s>>>(g);
   timer_end(GNN_K_GEMM_REDUCE, 0.0, s);
   return hipGetLastError();
 }
@@ -2145,7 +2153,7 @@ hipError_t gemm_launch(const GemmBatch& b, void* workspace, size_t ws_bytes,
   timer_end(kid, gemm_flops(b), s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !streamk) return e;
-  if (defer) {  // the next launch (or gemm_flush) sums the shared tiles
+  if (defer && g.bn == BN) {  // the next launch (or gemm_flush) sums the shared tiles
     memcpy(defer->args, &g, sizeof(g));
     defer->pending = 1;
     return hipSuccess;
