@@ -362,6 +362,8 @@ struct SpmmArgs {
   int64_t ld_mask;
   int32_t nslices;  // column slices, none empty
   int32_t share;    // XCDs of a slice of its own (0 for more than 8 slices)
+  int32_t own;      // XCDs with a slice of their own
+  uint32_t own_slice, own_sub;  // 4 bits per XCD: its slice, which of the share
   int32_t per;      // blocks per XCD
   int32_t sw;       // slice width in columns
   int32_t nwin;     // workgroups per slice: plan windows / wpb, rounded up
@@ -393,14 +395,13 @@ struct SpmmArgs {
 // more slices than XCDs every XCD takes an eighth of them all, in order.
 __device__ inline bool slice_of(const SpmmArgs& a, int& slice, int& win) {
   const int x = blockIdx.x & 7, q = blockIdx.x >> 3;
-  const int own = a.share * a.nslices;
-  if (x < own) {
-    slice = x % a.nslices;
-    win = q * a.share + x / a.nslices;
+  if (x < a.own) {
+    slice = (a.own_slice >> (4 * x)) & 15;
+    win = q * a.share + ((a.own_sub >> (4 * x)) & 15);
   } else {
     const int first = a.share * a.per, rem = a.nwin - first;
     if (rem <= 0) return false;
-    const uint32_t l = (uint32_t)(x - own) * (uint32_t)a.per + (uint32_t)q;
+    const uint32_t l = (uint32_t)(x - a.own) * (uint32_t)a.per + (uint32_t)q;
     slice = (int)(l / (uint32_t)rem);
     win = first + (int)(l % (uint32_t)rem);
   }
@@ -971,6 +972,11 @@ static SpmmArgs spmm_args(const SpmmCall& c, bool* vec_out, bool* off32_out) {
   a.wpb = d.nblk * a.nslices > 16384 ? 2 : 1;
   a.nwin = (int32_t)ceil_div(d.nblk, (int64_t)a.wpb);
   a.share = 8 / a.nslices;
+  a.own = a.share * a.nslices;
+  for (int x = 0; x < a.own; ++x) {
+    a.own_slice |= (uint32_t)(x % a.nslices) << (4 * x);
+    a.own_sub |= (uint32_t)(x / a.nslices) << (4 * x);
+  }
   // One XCD left over (seven slices) fetches the rows of all slices anew; with
   // wide slices and few gathers of a row in its eighth of the windows it is
   // the last to end, and stays idle instead: 8,000 x 448, 17 entries a row,
