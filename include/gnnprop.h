@@ -211,10 +211,11 @@ gnn_status gnn_csr_validate_noalloc(const gnn_csr* csr,
 
 /* Device bytes the forward pass saves for the backward pass, and the
  * scratch bytes forward and backward need.  Order 1 saves A_s X (n x f_in
- * floats).  With split products (neither product flag) the forward's weight
- * split also writes the bf16 pieces of W_self^T and W_neigh^T that the input
- * gradient's product uses (3 x 2 x ceil(h / 16) x 16 x f_in bytes each), so
- * that the backward pass does not split the weights again; with
+ * floats).  With split products (neither product flag) there is also room
+ * for the bf16 pieces of W_self^T and W_neigh^T (3 x 2 x ceil(h / 16) x 16 x
+ * f_in bytes each); where the input gradient's product takes pieces, the
+ * forward's weight split writes them, so that the backward pass does not
+ * split the weights again.  With
  * GNN_FLAG_BF16 or GNN_FLAG_F32_MFMA order 2 saves nothing.  Both sizes
  * depend only on csr->n, csr->nnz, the layer shape, its order and its
  * product flag. */
@@ -249,9 +250,9 @@ gnn_status gnn_prop_fwd(const gnn_csr* csr, const gnn_layer* layer,
  * Needs csr->values, csr->values_t and csr->plan, and the `saved` buffer of
  * the matching gnn_prop_fwd call with the same layer (same order and product
  * flag) and the same weights: with split products the input gradient takes
- * the weights' pieces saved by that call (as in training, where the
- * backward pass follows the forward pass that used the weights).  Outputs
- * must not overlap inputs. */
+ * either the weights or their pieces saved by that call (as in training,
+ * where the backward pass follows the forward pass that used the weights).
+ * Outputs must not overlap inputs. */
 gnn_status gnn_prop_bwd(const gnn_csr* csr, const gnn_layer* layer,
                         const float* X, const float* W_self,
                         const float* W_neigh, const float* Y, const float* dY,

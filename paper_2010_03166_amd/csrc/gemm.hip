@@ -39,7 +39,8 @@
 // rows are stored in the order (k mod 16) * 2 + k / 16 so that the two lane
 // halves of a step read adjacent rows (different LDS banks).
 //
-// Work split (gemm_shape).  One block per tile when the tiles fill the 512
+// Work split (general_shape; planes_shape for B given as pieces).  One block
+// per tile when the tiles fill the 512
 // resident slots (2 per CU), or come to about one per CU over a short K;
 // split-K (one (tile, K range) per block) for few tiles over a long K
 // (weight gradients, K = n); otherwise stream-K: the launch's tiles x
@@ -1254,10 +1255,11 @@ __global__ __launch_bounds__(NW * 64, NW / 2) void gemm_split_kernel(GemmKArgs g
 //
 // The split-product kernel of the launches whose B comes as ready pieces
 // (GemmSeg::Bp): forward products and input gradients.  What bounds these
-// launches is power: with random operands the matrix cores sustain 1,860
-// TFLOP/s of 32 x 32 x 16 bf16 MFMAs and 2,110 of 16 x 16 x 32 ones
-// (register operands only; 2,470 of either with constant operands), so this
-// kernel multiplies with the latter, 32 k per stage.
+// launches is power: with random operands the matrix cores sustain 1,760
+// TFLOP/s of 32 x 32 x 16 bf16 MFMAs at 1.76 GHz and 2,000 of 16 x 16 x 32
+// ones at 2.02 GHz (register operands only; 2,460 and 2,400 at 2.4 GHz with
+// constant operands), so this kernel multiplies with the latter, 32 k per
+// stage.
 // Lane group g = lane / 16 supplies k = 8 g + j (j = 0..7) in both operands.
 //   A K-contiguous: LDS plane [x][k] rows of 16 words (k pairs) + 4 words of
 //     padding (80 bytes: eight consecutive rows of a 128-bit fragment read
@@ -1270,10 +1272,11 @@ __global__ __launch_bounds__(NW * 64, NW / 2) void gemm_split_kernel(GemmKArgs g
 //   B: fragments straight from the planes in global memory (two runs of 512
 //     consecutive bytes each), one stage ahead.
 // Four wavefronts per block, each 64 x 16 NJ of the 128 x 32 NJ tile.
-// Measured (8000 x 1024, K = 1024 / 608; 50000 x 1024, K = 2048), against
-// eight wavefronts of 32 x 32 x 16 MFMAs, 16 k per stage: 89 / 56 / 1,082 us,
-// before 95 / 59 / 1,127.  At K = 4096 the shader clock rises from 1.68 to
-// 1.98 GHz for the same work.
+// Measured (gnn_gemm, whole call, 8000 x 1024, K = 1024 / 608; 50000 x 1024, K =
+// 2048), against eight wavefronts of 32 x 32 x 16 MFMAs, 16 k per stage: 89 /
+// 59 / 995 us, before 95 / 62 / 1,070.
+// Registers: at 128 columns 50 and at 96 columns 8 of them are spilled, stored
+// before the pipelined loop and loaded after it; the loop itself uses none.
 constexpr int BKP = 32;
 constexpr int KCP_ROW = 20;
 constexpr int KCP_PLANE = 128 * KCP_ROW;
@@ -1384,9 +1387,11 @@ __device__ inline void store_acc16(const GemmProblem& P, const TileInfo& ti, int
 // out when they add to a larger accumulator; so the error of one long sum
 // stays below that of the partial sums of a split one (K = 1024: 1.2e-7 of
 // |C|, 2.4e-7 in four parts, 4.9e-7 in one without this).  The additions cost
-// 3 % where a block has its CU to itself, 20 % where two share one.
+// 5 % at 64 columns; 96 and 128 have no registers for the second sum (96 with
+// it spilled 56 and took 1.47 times a stage's time).
 template <bool AT, int NJ, bool CHAIN>
 __global__ __launch_bounds__(256, 2) void gemm_planes_kernel(GemmKArgs g, GemmKArgs fx) {
+  static_assert(!CHAIN || NJ == 2, "no registers");
   if (run_pending_fixup(g, fx)) return;
   constexpr int BNT = 32 * NJ;
   constexpr bool A_KC = !AT;

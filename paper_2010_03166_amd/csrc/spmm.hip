@@ -868,9 +868,9 @@ static void spmm_epi(const SpmmArgs& a, bool off32, hipStream_t s) {
 // Lane group width for a slice row of `units` float4s (or floats): a power
 // of two covering it, or 12 or 20 lanes (48- and 80-column slices: five and
 // three groups to a wavefront, 4 idle lanes of 64, where 16 and 32 lanes
-// would leave 16 and 24 idle).  RAG: float4
-// lanes on a width that is not a multiple of 4 (the lane at the row's end
-// writes its 1..3 columns one by one).
+// would leave 16 and 24 idle; 20,000 x 384 without a degree cap 113 -> 102 us,
+// with one 75 -> 78).  RAG: float4 lanes on a width that is not a multiple of
+// 4 (the lane at the row's end writes its 1..3 columns one by one).
 template <bool VEC, bool RAG>
 static void spmm_dispatch(const SpmmArgs& a, bool off32, hipStream_t s) {
   const int units = VEC ? ceil_div(a.sw, 4) : a.sw;  // column vectors per slice row

@@ -109,6 +109,39 @@ def test_two_segment_input_gradient(n, f, h):
     assert (err <= bound).all(), float((err / bound).max())
 
 
+@pytest.mark.parametrize("f,h", [(16, 512), (1024, 16), (512, 16), (16, 96), (602, 512)])
+@pytest.mark.parametrize("order", [1, 2])
+def test_layer_with_pieces_in_one_direction_only(f, h, order):
+    """Wide outputs of few stages go to the kernel that splits the weight
+    itself, forward and input gradient each by its own shape (identity graph;
+    bounds as above)."""
+    n = 6001
+    dg = runtime.DeviceGraph(synth.identity_graph(n))
+    dg.prepare()
+    gen = torch.Generator().manual_seed(f + h)
+    st = runtime.SageStack(dg, [synth.LayerParams(
+        *(torch.randn((f, h), generator=gen).numpy() for _ in range(2)))], f, order=order)
+    L = st.layers[0]
+    x = runtime.padded(torch.randn((n, f), generator=gen).cuda(), -(-f // 16) * 16)
+    y = st.forward(x)
+    dy = runtime.padded(torch.randn((n, 2 * h), generator=gen).cuda(), L["Y"].stride(0))
+    dx = st.backward(dy)
+    torch.cuda.synchronize()
+    w = torch.cat([L["W_self"], L["W_neigh"]], 1).cpu().double()
+    xd, g = x.cpu().double(), dy.cpu().double() * (y.cpu() > 0)
+
+    def check(got, a, b, k):
+        err = (got.cpu().double() - (a @ b).clamp_min(0) if got is y else
+               got.cpu().double() - a @ b).abs()
+        bound = (12 * -(-k // 32) + 16) * 2.0 ** -23 * (a.abs() @ b.abs())
+        assert (err <= bound).all(), float((err / bound.clamp_min(1e-30)).max())
+
+    check(y, xd, w, f)
+    check(dx, g, w.T, 2 * h + 64)
+    check(L["dW_self"], xd.T, g[:, :h], n)
+    check(L["dW_neigh"], xd.T, g[:, h:], n)
+
+
 # every way the work split takes a product of 512 rows and more
 WAYS = [
     (512, 64, 64),      # whole tiles of 64 columns, one chain over K
